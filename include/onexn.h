@@ -91,8 +91,9 @@ onexn_status onexn_build_mask(const void* w, onexn_dtype wdt, int32_t n, int32_t
  *           onexn_mask_workspace_bytes(n, m, N) bytes, 8-byte aligned, owned by
  *           the caller; nothing in it needs initialising, and it must not be
  *           reused until the work enqueued here has finished.
- * stream:   hipStream_t (NULL = the null stream).  Enqueues four kernels and
- *           returns without waiting.
+ * stream:   hipStream_t (NULL = the null stream).  Enqueues its kernels (up
+ *           to seven) and returns without waiting; mask_dev holds
+ *           intermediate counts until the last one has run.
  * Errors:   NULL, DTYPE, ARG (sizes, N < 1, p outside [0, 1], misaligned
  *           workspace), BUFSIZE (too small a workspace, layer beyond int32
  *           indexing), HIP (launch failed).  On an error nothing is enqueued

@@ -113,3 +113,34 @@ def test_workspace_errors():
     assert lib.onexn_build_mask_dev(*args, ws.data_ptr(), need, None) == 0
     torch.cuda.synchronize()
     assert t.value == 16 * 4 // 2
+
+
+@pytest.mark.parametrize("kind", ["normal", "ties", "equal", "nan"])
+@pytest.mark.parametrize("blocks", [512, 513, 2048, 2049, 16383, 16384, 32767, 32768, 262144])
+def test_selection_sizes(blocks, kind):
+    """Block counts at the edges of the selection's variants (one workgroup, spread
+    over workgroups with the smaller and larger lists), with distinct scores, with
+    many equal ones, with all equal (more than the lists hold) and
+    with NaN and infinite ones."""
+    gen = torch.Generator().manual_seed(blocks)
+    n = {16383: 3, 32767: 7}.get(blocks, 1 if blocks % 2 else 4)
+    w = torch.randn(n, blocks // n, 1, 1, generator=gen)
+    if kind == "ties":
+        w = (w * 64).round() / 64
+    elif kind == "equal":
+        w = torch.full_like(w, -0.375)
+    elif kind == "nan":
+        w[0, 5::7], w[-1, 3::11] = float("nan"), float("inf")
+    for p in (0.0, 0.013, 0.5, 0.7, 1.0):
+        if kind != "nan":
+            _check(w, 1, p, True)
+            continue
+        perm, mask, t = onexn.build_mask_dev(w.cuda(), 1, p, True)
+        # The host rejects NaN; the order is by |w| with NaN above +inf, then by index.
+        perm, mask = perm.cpu().long(), mask.cpu()
+        assert sorted(perm.tolist()) == list(range(n))
+        key = w[perm, :, 0, 0].abs().double().t().reshape(-1)
+        key = torch.where(key.isnan(), torch.full_like(key, 2.0), torch.where(key.isinf(), torch.full_like(key, 1.0), key / 100))
+        ref = torch.zeros(blocks, dtype=torch.uint8)
+        ref[torch.sort(key, descending=True, stable=True).indices[:t]] = 1
+        assert torch.equal(mask.reshape(-1), ref)
