@@ -154,6 +154,8 @@ onexn_status conv2d_fwd(const int32_t* P_dev, const int32_t* I_dev, const void* 
         if (tile && (pwk == 1 || !prefer_direct)) return launch_pw_tile(a, s);
         return launch_pw_direct(a, s);
     }
+    const bool kxk_forced = tuning(kTuneKxkSplit) >= 0 || tuning(kTuneKxkTp) >= 0;
+    if (!kxk_forced && !generic_forced() && planes_fwd_applies(a, xdt, ydt, layout)) return launch_planes_fwd(a, xdt, ydt, s);
     if (kxk_applies(a, xdt, ydt, layout) && !generic_forced()) return launch_kxk(a, s);
     if (pw_fma_applies(a, xdt, ydt, layout) && !generic_forced()) return launch_pw_fma(a, s);
     if (kxk_fma_applies(a, xdt, ydt, layout) && !generic_forced()) return launch_kxk_fma(a, s);

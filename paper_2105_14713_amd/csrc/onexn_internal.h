@@ -19,7 +19,8 @@ void clear_error();
 // Each is process-wide; kTuneAuto (the initial value) leaves the choice to
 // the dispatch rules.
 enum Tune : int {
-    kTuneKernel,       // 1: the generic gather kernels for every layer
+    kTuneKernel,       // 1: the generic gather kernels for every layer; 2: the bf16-plane
+                       // kernels for every fp32 layer that they can compute
     kTunePwKernel,     // 1x1 fp32 N = 16/32: 1 resident tile, 3 register-operand
     kTunePwWgs,        // resident-tile 1x1: workgroups
     kTunePwbGp,        // register-gathered bf16: pixels per granule (4, 8)

@@ -1,0 +1,184 @@
+"""The kernels on the bf16 matrix instructions (forward 1x1 and 3x3, input and
+weight gradients), which take bf16 operands as they are and fp32 ones as three
+bf16 planes: integer-exact against the oracle at the edges of their tiles,
+fp32 error against 64 bits, and operands that are not finite."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2105_14713_amd as onexn
+import workloads
+from gpu_helpers import gpu_conv, oracle_conv
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    onexn.load_library()
+
+
+DTYPES = {"f32": torch.float32, "bf16": torch.bfloat16}
+FWD = [  # (n, m, k, stride, pad, B, H, W, N)
+    (40, 33, 3, 1, 1, 1, 16, 16, 32),    # one 256-pixel tile exactly, a ragged col-group
+    (64, 50, 3, 1, 1, 3, 14, 14, 32),    # tiles spanning images
+    (32, 20, 3, 1, 0, 9, 4, 4, 32),      # the narrowest images, many per tile
+    (32, 90, 3, 1, 2, 5, 5, 6, 16),      # padding wider than the window's reach
+    (48, 17, 3, 1, 1, 1, 7, 200, 16),    # several strips of columns, the last narrower
+    (64, 40, 3, 1, 1, 1, 19, 61, 32),
+    (33, 70, 3, 1, 1, 2, 31, 8, 16),
+    (64, 45, 3, 2, 1, 2, 15, 17, 32),    # parity planes (bf16)
+    (48, 24, 3, 2, 0, 1, 9, 70, 16),
+    (32, 18, 3, 3, 1, 2, 13, 11, 16),
+    (32, 18, 3, 5, 2, 2, 13, 21, 32),    # stride beyond the window
+    (70, 130, 1, 1, 0, 2, 9, 7, 16),     # 1x1, pixels not a multiple of four (bf16)
+    (70, 130, 1, 1, 0, 2, 8, 34, 16),    # quads, more than one tile per image
+    (64, 40, 1, 2, 0, 3, 9, 11, 32),
+    (32, 65, 1, 3, 2, 1, 10, 8, 16),
+]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("n,m,k,s,pd,B,H,W,N", FWD)
+def test_forward_integers(n, m, k, s, pd, B, H, W, N, dt, tune):
+    tune("kernel", 2)
+    w, x = workloads.gen_integer_layer(n + m + W, n, m, k, B, H, W)
+    for p in (0.0, 0.5, 0.9):
+        y, _ = gpu_conv(w.to(DTYPES[dt]), x.to(DTYPES[dt]), N, p, True, s, pd, out_dtype=torch.float32)
+        ref, _ = oracle_conv(w, x, N, p, True, s, pd)
+        np.testing.assert_array_equal(y, ref)
+
+
+BWD = [  # (n, m, k, stride, pad, B, H, W, N)
+    (40, 33, 3, 1, 1, 2, 16, 16, 32),
+    (64, 50, 3, 1, 1, 3, 14, 14, 16),
+    (72, 20, 3, 1, 0, 7, 6, 6, 8),
+    (32, 40, 3, 1, 2, 2, 5, 7, 16),
+    (32, 129, 3, 1, 1, 1, 9, 61, 32),
+    (80, 45, 1, 1, 0, 3, 7, 9, 32),
+    (140, 270, 1, 1, 0, 2, 8, 8, 16),
+    (64, 33, 1, 1, 1, 2, 6, 5, 8),
+    (48, 40, 3, 2, 1, 2, 11, 17, 16),    # weight gradient only: strided octets
+    (32, 70, 1, 2, 0, 2, 13, 9, 32),
+    (32, 5, 5, 1, 2, 1, 11, 23, 16),
+    (32, 3, 7, 3, 3, 2, 25, 26, 32),
+    (32, 600, 1, 1, 0, 40, 5, 5, 32),    # several chunks of 512 pixels
+]
+
+
+def _grads(w, x, dy, N, p, s, pd):
+    n, m, k, _ = w.shape
+    L = onexn.prepare_layer(w, N, p, True)
+    dx = torch.full(x.shape, float("nan"), device="cuda")
+    dD = torch.full((L.t, N, k, k), float("nan"), device="cuda")
+    onexn.conv2d_bwd_data(L.P, L.I, L.D, n, m, dy.cuda(), x.shape[2:], s, pd, torch.float32, out=dx)
+    onexn.conv2d_bwd_weight(L.P, L.I, n, N, (k, k), x.cuda(), dy.cuda(), s, pd, out=dD)
+    return L, dx.double().cpu().numpy(), dD.double().cpu().numpy()
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("n,m,k,s,pd,B,H,W,N", BWD)
+def test_gradients_integers(n, m, k, s, pd, B, H, W, N, dt):
+    w, x = workloads.gen_integer_layer(n + m + W, n, m, k, B, H, W)
+    Ho, Wo = onexn.out_hw(H, W, k, k, (s, s), (pd, pd))
+    dy = torch.randint(-3, 4, (B, n, Ho, Wo), generator=torch.Generator().manual_seed(W)).float()
+    for p in (0.0, 0.5, 0.95):
+        L, dx, dD = _grads(w.to(DTYPES[dt]), x.to(DTYPES[dt]), dy.to(DTYPES[dt]), N, p, s, pd)
+        pr = oracle.prune(w.double().numpy(), N, p, True)
+        np.testing.assert_array_equal(
+            dx, oracle.conv2d_bwd_data(dy.double().numpy(), pr.wbar, (H, W), (s, s), (pd, pd)))
+        dw = oracle.conv2d_bwd_weight(x.double().numpy(), dy.double().numpy(), pr.T, N, (k, k), (s, s), (pd, pd))
+        np.testing.assert_array_equal(dD, oracle.pack(dw, pr.T, N)[2])
+
+
+def test_bf16_weight_gradient_does_not_vary():
+    w, x = workloads.gen_integer_layer(3, 64, 48, 3, 4, 20)
+    x, dy = torch.randn(4, 48, 20, 20).bfloat16(), torch.randn(4, 64, 20, 20).bfloat16()
+    runs = [_grads(w.bfloat16(), x, dy, 32, 0.5, 1, 1)[2] for _ in range(3)]
+    assert all(np.array_equal(runs[0], r) for r in runs[1:])
+
+
+def _norm_err(a, b):
+    return np.linalg.norm(a - b) / np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** 60, 2.0 ** -60])
+@pytest.mark.parametrize("N", [16, 32])
+def test_fp32_error(N, scale, tune):
+    """Three planes hold an fp32 value exactly, the six products leave out less
+    than 3 * 2^-24 of a product, and each of at most 9 * 256 / 16 additions per
+    accumulator rounds by 2^-24 of a partial sum, at random: together under
+    sqrt(144) * 2^-24 = 7e-7 of the result's norm, at any scale."""
+    tune("kernel", 2)
+    gen = torch.Generator().manual_seed(N)
+    w = torch.randn(64, 256, 3, 3, generator=gen) * 0.03
+    x = torch.randn(2, 256, 14, 14, generator=gen).clamp_min(0) * scale
+    y, _ = gpu_conv(w, x, N, 0.3, False, 1, 1)
+    ref, _ = oracle_conv(w, x, N, 0.3, False, 1, 1)
+    assert _norm_err(y / scale, ref / scale) < 7e-7
+    dy = torch.randn(2, 64, 14, 14, generator=gen) * scale
+    _, dx, _ = _grads(w, x, dy, N, 0.3, 1, 1)
+    pr = oracle.prune(w.double().numpy(), N, 0.3, True)
+    ref = oracle.conv2d_bwd_data(dy.double().numpy(), pr.wbar, (14, 14), (1, 1), (1, 1))
+    assert _norm_err(dx / scale, ref / scale) < 7e-7
+
+
+def _kept_grads(L, x, dy, k, s, pd):
+    """Both gradients in fp64 over the kept blocks and in-image taps only."""
+    n, N = L.n, L.N
+    P, I, D = L.P.cpu().numpy(), L.I.cpu().numpy(), L.D.double().cpu().numpy()
+    B, m, H, W = x.shape
+    Ho, Wo = dy.shape[2:]
+    dx, dD = np.zeros(x.shape), np.zeros(D.shape)
+    for g in range(len(P) - 1):
+        rows = min(N, n - g * N)
+        d = dy[:, g * N:g * N + rows]
+        for z in range(P[g], P[g + 1]):
+            for q in range(k):
+                oh = [o for o in range(Ho) if 0 <= o * s - pd + q < H]
+                ih = [o * s - pd + q for o in oh]
+                for r in range(k):
+                    ow = [o for o in range(Wo) if 0 <= o * s - pd + r < W]
+                    iw = [o * s - pd + r for o in ow]
+                    part = d[:, :, oh][:, :, :, ow]
+                    if not oh or not ow:
+                        continue
+                    dx[np.ix_(range(B), [I[z]], ih, iw)] += np.einsum("bohw,o->bhw", part, D[z, :rows, q, r])[:, None]
+                    xs = x[:, I[z]][:, ih][:, :, iw]
+                    dD[z, :rows, q, r] = np.einsum("bohw,bhw->o", part, xs)
+    return dx, dD
+
+
+def _same(got, ref):
+    """Non-finite values in the same places and of the same kind, finite ones close."""
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(got)], ref[np.isinf(ref)])
+    f = np.isfinite(ref)
+    assert np.array_equal(f, np.isfinite(got))
+    assert np.abs(got[f] - ref[f]).max() <= 1e-5 * np.abs(ref[f]).max()
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("k,N", [(3, 32), (3, 16), (1, 32), (1, 16)])
+def test_not_finite(k, N, dt, tune):
+    tune("kernel", 2)
+    w, x = workloads.gen_integer_layer(k + N, 2 * N, 24, k, 2, 12, 10)
+    dy = torch.randint(1, 4, (2, 2 * N, 12, 10), generator=torch.Generator().manual_seed(N)).float()
+    x[0, 3, 4, 5], x[1, 7, 0, 0], x[1, 9, 11, 9] = float("inf"), float("-inf"), float("nan")
+    dy[0, 5, 0, 0], dy[1, N + 1, 6, 9], dy[1, 2, 11, 4] = float("inf"), float("nan"), float("-inf")
+    w, x, dy = (v.to(DTYPES[dt]) for v in (w, x, dy))
+    L = onexn.prepare_layer(w, N, 0.5, True)
+    y = L.forward(x.cuda(), 1, k // 2, out_dtype=torch.float32).double().cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        _same(y, oracle.decode(x.double().numpy(), L.P.cpu().numpy(), L.I.cpu().numpy(),
+                               L.D.double().cpu().numpy(), L.n, (1, 1), (k // 2, k // 2)))
+        if dt == "f32" and k == 1:
+            return      # those gradients run on the fp32 instruction
+        L, dx, dD = _grads(w, x, dy, N, 0.5, 1, k // 2)
+        rdx, rdD = _kept_grads(L, x.double().numpy(), dy.double().numpy(), k, 1, k // 2)
+        _same(dx, rdx)
+        if dt == "bf16":
+            _same(dD, rdD)
