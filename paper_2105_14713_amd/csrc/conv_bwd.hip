@@ -432,6 +432,8 @@ extern "C" onexn_status onexn_conv2d_bwd_weight(const int32_t* P_dev, const int3
     if (t == 0) return ONEXN_OK;
     a.I = I_dev;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (tuning(kTuneBwdKernel) != 1 && bwd_weight_bf16_applies(a, xdt, batch))
+        return launch_bwd_weight_bf16(a, batch, x_dev, dy_dev, dD_dev, s);
     // 1x1 stride-1 fp32 layers at N = 16 / 32: the matrix-core kernel.
     if (bwd_weight_pw_applies(a, xdt, batch) && tuning(kTuneBwdKernel) != 1)
         return launch_bwd_weight_pw(a, x_dev, dy_dev, dD_dev, s);

@@ -232,6 +232,10 @@ onexn_status launch_planes_dx(const ConvArgs& a, onexn_dtype wdt, onexn_dtype dx
 onexn_status launch_kxk_fma(ConvArgs a, hipStream_t stream);
 onexn_status launch_kxk(ConvArgs a, hipStream_t stream);
 
+bool bwd_weight_bf16_applies(const ConvArgs& a, onexn_dtype xdt, int32_t batch);
+onexn_status launch_bwd_weight_bf16(const ConvArgs& a, int32_t batch, const void* x, const void* dy, float* dD,
+                                    hipStream_t stream);
+
 // Launches `kernel` on a 1-D grid of `total` workgroups.
 template <typename K>
 onexn_status launch_grid(K kernel, ConvArgs& a, int64_t total, hipStream_t stream,
