@@ -401,12 +401,15 @@ extern "C" onexn_status onexn_conv2d_bwd_data(const int32_t* P_dev, const int32_
     a.D = D_dev;
     hipStream_t s = static_cast<hipStream_t>(stream);
     // fp32 layers with at most four input channels: one lane per input pixel
-    // and all its channels.  3x3 stride-1 layers and bf16 1x1 ones at N >= 8:
-    // the bf16-plane kernel (fp32 1x1 layers multiply too little per staged
-    // value for it: 64 -> 256 at 56x56, batch 64, 167 us against 96).  Other
-    // fp32 1x1 and 3x3 layers: the fp32 matrix-core kernels.
+    // and all its channels.  bf16 1x1 layers at N >= 8: a kernel of their own.
+    // 3x3 layers (fp32: stride 1) at N >= 8: the bf16-plane kernel (fp32 1x1
+    // layers multiply too little per staged value for it: 64 -> 256 at 56x56,
+    // batch 64, 167 us against 96).  Other fp32 1x1 and 3x3 layers: the fp32
+    // matrix-core kernels.
     if (tuning(kTuneBwdKernel) != 1) {
         if (bwd_data_fewc_applies(a, wdt, dxdt, batch)) return launch_bwd_data_fewc(a, batch, dy_dev, dx_dev, s);
+        if (bwd_data_pw_bf16_applies(a, wdt, batch))
+            return launch_bwd_data_pw_bf16(a, dxdt, batch, dy_dev, dx_dev, s);
         if (tuning(kTuneBwdKernel) < 0 && planes_dx_applies(a, wdt, batch)) return launch_planes_dx(a, wdt, dxdt, batch, dy_dev, dx_dev, s);
         if (bwd_data_pw_applies(a, wdt, dxdt, batch)) return launch_bwd_data_pw(a, dy_dev, dx_dev, s);
     }

@@ -232,6 +232,9 @@ onexn_status launch_planes_dx(const ConvArgs& a, onexn_dtype wdt, onexn_dtype dx
 onexn_status launch_kxk_fma(ConvArgs a, hipStream_t stream);
 onexn_status launch_kxk(ConvArgs a, hipStream_t stream);
 
+bool bwd_data_pw_bf16_applies(const ConvArgs& a, onexn_dtype wdt, int32_t batch);
+onexn_status launch_bwd_data_pw_bf16(const ConvArgs& a, onexn_dtype dxdt, int32_t batch, const void* dy, void* dx,
+                                     hipStream_t stream);
 bool bwd_weight_bf16_applies(const ConvArgs& a, onexn_dtype xdt, int32_t batch);
 onexn_status launch_bwd_weight_bf16(const ConvArgs& a, int32_t batch, const void* x, const void* dy, float* dD,
                                     hipStream_t stream);

@@ -1,7 +1,7 @@
 // Convolutions of a 1xN-pruned layer, NCHW, on the bf16 matrix instructions:
-// forward (N in {16, 32}) and input gradient (stride 1; N >= 8) of 3x3 layers,
-// for bf16 operands and for fp32 ones as three bf16 planes (planes.h; fp32
-// forward at stride 1), and both of 1x1 layers in bf16.
+// forward (N in {16, 32}) and input gradient (N >= 8) of 3x3 layers, for bf16
+// operands and, at stride 1, for fp32 ones as three bf16 planes (planes.h),
+// and the forward of bf16 1x1 layers.
 //
 // Paper: Lin et al., "1xN Pattern for Pruning Convolutional Neural Networks"
 // (arXiv 2105.14713), Sec. 3.4 (Eq. 8 over P, I, D) and Sec. 4.1 (fine-tuning
@@ -9,7 +9,7 @@
 //
 // Work.  A workgroup of four waves computes a tile of destination pixels for
 // one block of rows: forward, the N output channels of one col-group, over
-// its kept blocks; input gradient, 32 or 128 input channels, over all output
+// its kept blocks; input gradient, 32 input channels, over all output
 // channels (Omega-bar's transpose as a dense operand, zero where pruned).  It
 // walks the contraction in chunks of OCT octets (8 source channels each):
 // the next chunk's values are loaded into registers while this one is
@@ -41,6 +41,12 @@
 // instruction, 64 here; its input gradient 188 and 118.  bf16: the latency of
 // a chunk's loads, one chunk ahead (two to four workgroups per unit).
 //
+// Input gradient of a strided layer: dY's pixels lie `dil` = stride apart in
+// the staged tile, with zeros between them.  Of the nine taps a pixel then
+// multiplies, one, two or four are not zero; the general kernel, which is the
+// other choice for bf16, has no matrix cores (256 -> 256 3x3 stride 2 at 14x14,
+// batch 64: 3474 us against 56).
+//
 // Non-finite results.  Planes of infinities are NaN, and the dense gradient
 // multiplies pruned zeros; a wave that ends with an accumulator that is not
 // finite computes its outputs again in plain fp32 over the kept blocks only.
@@ -64,6 +70,7 @@ struct PlArgs {
     int32_t C, R;             // source and destination channels
     int32_t H, W, Ho, Wo;     // source and destination images
     int32_t batch, s, ph, pw; // stride (1 for the gradient), padding (may be negative there)
+    int32_t dil;              // distance of source pixels (the gradient's stride; 1 forward)
     int32_t rows;             // batch * Ho
     int32_t tw, tps, rblocks; // strip width, tiles per strip, row blocks
     int32_t total;
@@ -73,9 +80,9 @@ struct PlArgs {
 };
 
 constexpr int kPlThreads = 256;
-// (col-group, 32-channel tile) runs of the gradient's index (3x3 on fp32: two
-// workgroups of 81792 bytes of LDS fit a compute unit).
-constexpr int pl_max_runs(int K) { return K == 1 ? 1024 : 240; }
+// Col-groups of the gradient's index in LDS (fp32: two workgroups of 81792
+// bytes fit a compute unit).
+constexpr int kPlMaxRuns = 240;
 
 // Entries (positions, weights) are stored by residue modulo 4: entry e at unit
 // (e % 4) * Q + e / 4.  A lane writes four consecutive entries, so with plain
@@ -88,13 +95,12 @@ template <int Q> __device__ __forceinline__ int32_t unit_of(int32_t e) { return 
 // Shape of a kernel's instance.  QUAD: four neighbouring source columns per
 // lane and load (3x3; 1x1 with stride 1, no padding and images of a multiple
 // of four pixels), else one position per lane.
-template <typename TX, int N, int K, int NBW, int XCAP, int UQ, int WM, bool QUAD>
+template <typename TX, int N, int K, int NBW, int XCAP, int UQ, bool QUAD>
 struct PlShape {
     static constexpr int NP = Planes<TX>::NP;
     static constexpr int KK = K * K;
     static constexpr int OCT = K == 1 ? 4 : 2;           // octets per chunk
-    static constexpr int ROWS = N * WM;
-    static constexpr int TP = (4 / WM) * 32 * NBW;       // pixels per tile
+    static constexpr int TP = 4 * 32 * NBW;       // pixels per tile
     static constexpr int WPO = 4 / OCT;                  // waves that stage an octet
     static constexpr int XP = K == 1 ? TP : XCAP;        // staged positions (capacity)
     static constexpr int QX = up_to(XP / 4, 4);          // units of a residue's positions,
@@ -102,7 +108,7 @@ struct PlShape {
     static constexpr int PER = QUAD ? 4 : 1;             // positions per item
     static constexpr int UX = K == 1 ? (TP + 64 * PER - 1) / (64 * PER) : UQ;   // items per thread
     static constexpr int XITEMS = 64 * WPO * UX;         // items per octet (capacity)
-    static constexpr int WE = ROWS * KK;                 // weight entries row * KK + tap
+    static constexpr int WE = N * KK;                    // weight entries row * KK + tap
     static constexpr int QW = up_to(WE / 4, 12);
     static constexpr int WU = 4 * QW;
     // Steps: N = 16 multiplies taps in pairs (K = 32), the tenth with zeros.
@@ -111,47 +117,11 @@ struct PlShape {
     static_assert(K == 1 || QUAD, "3x3 tiles are staged in quads");
 };
 
-// Rows below c0 in a col-group: first entry of [zb, ze) with I >= c0.
-__device__ __forceinline__ int32_t lower_entry(const int32_t* __restrict__ I, int32_t zb, int32_t ze, int32_t c0) {
-    int32_t lo = zb, hi = ze;
-    while (hi - lo > 16) {                               // 16 independent samples a round
-        const int32_t step = (hi - lo + 15) / 16;
-        int32_t below = 0;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int32_t e = lo + k * step;
-            below += (e < hi && I[min(e, ze - 1)] < c0) ? 1 : 0;
-        }
-        const int32_t nlo = below == 0 ? lo : lo + (below - 1) * step + 1;
-        hi = below == 0 ? lo : min(hi, lo + below * step);
-        lo = nlo;
-    }
-    int32_t below = 0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) below += (lo + k < hi && I[min(lo + k, ze - 1)] < c0) ? 1 : 0;
-    return lo + below;
-}
-
 __device__ __forceinline__ float load_f(__amdgpu_buffer_rsrc_t r, int32_t v, int32_t s, float*) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, v, s, 0));
 }
 __device__ __forceinline__ uint32_t load_f(__amdgpu_buffer_rsrc_t r, int32_t v, int32_t s, uint16_t*) {
     return __builtin_amdgcn_raw_buffer_load_b16(r, v, s, 0);
-}
-// Eight consecutive weights (16-byte aligned); bf16 ones are the plane already.
-__device__ __forceinline__ void load_8(__amdgpu_buffer_rsrc_t r, int32_t v, float (&d)[8]) {
-    const f32x4 a = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, v, 0, 0));
-    const f32x4 b = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, v, 16, 0));
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        d[k] = a[k];
-        d[4 + k] = b[k];
-    }
-}
-__device__ __forceinline__ void load_8(__amdgpu_buffer_rsrc_t r, int32_t v, uint32_t (&d)[8]) {
-    const u32x4 a = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, v, 0, 0));
-#pragma unroll
-    for (int k = 0; k < 4; ++k) d[k] = a[k];
 }
 // Four consecutive values of a row as they are held between load and cut.
 template <typename T> struct Quad;
@@ -178,21 +148,20 @@ __device__ __forceinline__ void for_each_index(F&& f) {
 // from either neighbouring integer, more than its rounding.
 __device__ __forceinline__ int32_t small_div(int32_t i, float inv) { return int32_t((float(i) + 0.5f) * inv); }
 
-template <bool kDx, typename TX, typename TY, int N, int K, int NBW, int XCAP, int UQ, int WM, bool kS1, bool kQuad, bool kEp>
+template <bool kDx, typename TX, typename TY, int N, int K, int NBW, int XCAP, int UQ, bool kS1, bool kQuad, bool kEp>
 __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
-    typedef PlShape<TX, N, K, NBW, XCAP, UQ, WM, kQuad> S;
+    typedef PlShape<TX, N, K, NBW, XCAP, UQ, kQuad> S;
     typedef typename Planes<TX>::reg reg_t;
     typedef typename Quad<TX>::type quad_t;
     typedef PlaneMfma<N> M;
-    constexpr int NP = S::NP, KK = S::KK, OCT = S::OCT, ROWS = S::ROWS, ES = int(sizeof(TX));
+    constexpr int NP = S::NP, KK = S::KK, OCT = S::OCT, ES = int(sizeof(TX));
     constexpr int NB = NBW * 32 / M::COLS;               // MFMA column blocks per wave
     static_assert(!kDx || N == 32, "the gradient's row tiles are 32 channels");
-    static_assert(kDx || WM == 1, "a forward workgroup is one col-group");
     __shared__ u32x4 sX[OCT * NP * S::XU];
     __shared__ u32x4 sW[OCT * NP * S::WU];
     __shared__ float sEp[kEp ? 2 * N : 1];
-    __shared__ int32_t sFirst[kDx ? pl_max_runs(K) : 1];
-    __shared__ uint32_t sMask[kDx ? pl_max_runs(K) : 1];
+    __shared__ int32_t sFirst[kDx ? kPlMaxRuns : 1];
+    __shared__ uint32_t sMask[kDx ? kPlMaxRuns : 1];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -241,7 +210,9 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
         // Source columns [wlo, whi) of the strip's windows in quads; the last
         // quad of a row moves back into the image.
         const int32_t w0 = strip * a.tw * st - a.pw;     // column of ci = 0 in column plane 0
-        const int32_t wlo = max(0, w0), whi = max(wlo, min(a.W, w0 + (a.tw + E - 1) * st + PL));
+        const int32_t dil = kDx ? a.dil : 1;
+        const int32_t wlo = max(0, (w0 + dil - 1) / dil),
+                      whi = max(wlo, min(a.W, kDx ? max(0, w0 + a.tw + E - 1 + dil) / dil : w0 + (a.tw + E - 1) * st + PL));
         const int32_t nq = (whi - wlo + 3) / 4, nrow = PL * RT;
         const float inq = 1.f / float(max(nq, 1)), iR = 1.f / float(RT), is = 1.f / float(a.Ho + E);
         const int32_t L0 = min(a.Ho - oh0, r1 - r0 + 1) + E;
@@ -252,13 +223,13 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
             const int32_t qpl = kS1 ? 0 : small_div(row, iR), v = row - qpl * RT;
             const int32_t w = v - L0, dw = small_div(max(w, 0), is);
             const int32_t db = w < 0 ? 0 : 1 + dw, orow = w < 0 ? oh0 + v : w - dw * (a.Ho + E);
-            const int32_t ih = orow * st - a.ph + qpl;
-            const bool in = i < nrow * nq && ih >= 0 && ih < a.H;
+            const int32_t vh = orow * st - a.ph + qpl, ih = kDx ? vh / dil : vh;
+            const bool in = i < nrow * nq && vh >= 0 && ih < a.H && ih * dil == vh;
             xo[u] = in ? int32_t((int64_t(db) * x_img + ih * a.W + col) * ES) : 0;
             const int32_t base = qpl * qplane + v * vpitch;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int32_t c = col + k - w0;          // column among the strip's
+                const int32_t c = (col + k) * dil - w0;  // column among the strip's
                 const int32_t ci = kS1 ? c : small_div(max(c, 0), 1.f / float(st)), cpl = c - ci * st;
                 xp[u][k] = in && c >= 0 && cpl < PL && ci < a.tw + E ? unit_of<S::QX>(base + cpl * CH + ci) : -1;
             }
@@ -266,21 +237,20 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
     }
 
     // ---- Rows: a col-group's kept blocks (forward), or the index of the
-    // blocks that keep this tile's channels (gradient): of col-group g and
-    // 32-channel tile w, the first such block and the mask of its channels.
+    // blocks that keep this tile's channels (gradient): of col-group g, the
+    // first such block and the mask of its channels.
     int32_t zb = 0, ze = 0, nchunk;
-    const int32_t c0 = rb * ROWS;
+    const int32_t c0 = rb * N;
     if constexpr (kDx) {
-        for (int32_t i = tid; i < a.G * WM; i += kPlThreads) {
-            const int32_t g = i / WM, cb = c0 + 32 * (i - g * WM);
-            int32_t lo = max(0, min(a.P[g], a.t)), hi = max(lo, min(a.P[g + 1], a.t));
-            const int32_t first = lo < hi ? lower_entry(a.I, lo, hi, cb) : lo;
+        for (int32_t i = tid; i < a.G; i += kPlThreads) {
+            const int32_t lo = max(0, min(a.P[i], a.t)), hi = max(lo, min(a.P[i + 1], a.t));
+            const int32_t first = lo < hi ? lower_entry(a.I, lo, hi, c0) : lo;
             uint32_t mask = 0;
 #pragma unroll
             for (int k = 0; k < 32; ++k) {
                 const int32_t e = first + k;
                 const int32_t c = e < hi ? a.I[e] : INT32_MAX;
-                if (c >= cb && c < cb + 32 && c < a.R) mask |= 1u << (c - cb);
+                if (c >= c0 && c < c0 + 32 && c < a.R) mask |= 1u << (c - c0);
             }
             sFirst[i] = first;
             sMask[i] = mask;
@@ -356,17 +326,13 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
             if constexpr (kDx) {
                 const int32_t g = e0 / a.NG, ol = e0 - g * a.NG;
                 const int32_t row = e / KK, tap = e - row * KK;
-                const int32_t run = min(g, a.G - 1) * WM + min(row, S::ROWS - 1) / 32;
+                const int32_t run = min(g, a.G - 1);
                 const uint32_t mask = sMask[run];
                 const int32_t z = sFirst[run] + __popc(mask & ((1u << (row & 31)) - 1));
                 const bool kept = (e < S::WE) & (g < a.G) & ((mask >> (row & 31)) & 1);
                 const int32_t at = kept ? ((z * a.NG + ol) * KK + (KK - 1 - tap)) * ES : int32_t(kBufferOutOfRange);
-                if constexpr (K == 1) {
-                    load_8(rD, at, wv[u]);
-                } else {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) wv[u][j] = load_f(rD, at, j * KK * ES, static_cast<TX*>(nullptr));
-                }
+                for (int j = 0; j < 8; ++j) wv[u][j] = load_f(rD, at, j * KK * ES, static_cast<TX*>(nullptr));
             } else {
                 const uint32_t eo = e < S::WE / 4 ? uint32_t(4 * e * ES) : kBufferOutOfRange;
 #pragma unroll
@@ -400,10 +366,7 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
             }
         } else {
             constexpr int left = piece - 4 * CX, k = left / PW % 4, w = left / (4 * PW) * PW + left % PW;
-            if constexpr (kDx && K == 1) {
-                if constexpr (ES == 2) cw[w][0][k] = wv[w][k];
-                else cut_pair(wv[w][2 * k], wv[w][2 * k + 1], k, cw[w]);
-            } else if constexpr (kDx) {
+            if constexpr (kDx) {
                 cut_pair(wv[w][2 * k], wv[w][2 * k + 1], k, cw[w]);
             } else if constexpr (ES == 4) {
                 cut_pair(wq[w / 4][2 * k][w % 4], wq[w / 4][2 * k + 1][w % 4], k, cw[w]);
@@ -432,7 +395,7 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
     };
 
     // ---- Compute roles.
-    const int wm = wave % WM, wn = wave / WM;
+    const int wn = wave;
     const int kg = lane / M::COLS, col = lane % M::COLS;
     int32_t xb[NB][K];                                   // unit of block nb's pixel at tap (0, r)
 #pragma unroll
@@ -456,7 +419,7 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
     for (int q = 0; q < K; ++q) tq[q] = (kS1 ? q * CH : (q % st) * qplane + (q / st) * vpitch) / 4;
     int32_t wb[K == 1 ? 1 : 4];                          // unit of the lane's row at taps 0 .. 3
 #pragma unroll
-    for (int t = 0; t < (K == 1 ? 1 : 4); ++t) wb[t] = unit_of<S::QW>((wm * N + col) * KK + t);
+    for (int t = 0; t < (K == 1 ? 1 : 4); ++t) wb[t] = unit_of<S::QW>(col * KK + t);
     PlaneAcc<N, NP> acc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb].zero();
@@ -587,14 +550,15 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
 #pragma unroll 1
             for (int r = 0; r < M::ACC; ++r) {
                 const int rr = M::row(lane, r);
-                const int32_t o = c0 + wm * N + rr;      // destination channel
+                const int32_t o = c0 + rr;      // destination channel
                 if (o >= a.R) continue;
                 float v = 0.f;
                 auto taps = [&](int32_t c, int64_t w0) {
 #pragma unroll 1
                     for (int tap = 0; tap < KK; ++tap) {
-                        const int32_t ih = hb + tap / K, iw = wb + tap % K;
-                        const bool in = ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
+                        const int32_t vh = hb + tap / K, vw = wb + tap % K, dil = kDx ? a.dil : 1;
+                        const int32_t ih = vh / dil, iw = vw / dil;
+                        const bool in = vh >= 0 && ih < a.H && vw >= 0 && iw < a.W && ih * dil == vh && iw * dil == vw;
                         if (kDx && !in) continue;
                         const float xf = in ? to_f32(x[int64_t(c) * a.H * a.W + int64_t(ih) * a.W + iw]) : 0.f;
                         v = fmaf(xf, to_f32(D[w0 + (kDx ? KK - 1 - tap : tap)]), v);
@@ -603,9 +567,9 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
                 if constexpr (kDx) {
 #pragma unroll 1
                     for (int32_t g = 0; g < a.G; ++g) {
-                        const uint32_t mask = sMask[g * WM + wm];
+                        const uint32_t mask = sMask[g];
                         if (!((mask >> rr) & 1)) continue;
-                        const int64_t z = sFirst[g * WM + wm] + __popc(mask & ((1u << rr) - 1));
+                        const int64_t z = sFirst[g] + __popc(mask & ((1u << rr) - 1));
                         const int32_t lim = min(a.NG, a.C - g * a.NG);
 #pragma unroll 1
                         for (int32_t i = 0; i < lim; ++i) taps(g * a.NG + i, (z * a.NG + i) * KK);
@@ -630,7 +594,7 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
 #pragma unroll
         for (int r = 0; r < M::ACC; ++r) {
             const int rr = M::row(lane, r);
-            const int32_t o = c0 + wm * N + rr;
+            const int32_t o = c0 + rr;
             if (o < a.R) put(yp + int64_t(o) * HWo, rr, acc[nb].value(r));
         }
     }
@@ -649,26 +613,26 @@ int32_t pl_strip(int32_t TP, int32_t cap, int32_t items, const PlArgs& a, int32_
         nr = std::min<int64_t>(nr, a.rows);
         const int64_t nimg = std::min<int64_t>(a.batch, nr < 2 ? 1 : (nr - 2) / a.Ho + 2);
         const int64_t rows = PL * (nr + nimg * E);
-        const int64_t cols = std::min<int64_t>(a.W, (tw + E - 1) * a.s + PL);
+        const int64_t cols = std::min<int64_t>(a.W, ((tw + E - 1) * a.s + PL + a.dil - 1) / a.dil + (a.dil > 1 ? 1 : 0));
         if (rows * PL * ((tw + E + 3) / 4 * 4) <= cap && rows * ((cols + 3) / 4) <= items) return tw;
     }
     return 0;
 }
 
-template <bool kDx, typename TX, typename TY, int N, int K, int NBW, int XCAP, int UQ, int WM, bool kS1, bool kQuad,
+template <bool kDx, typename TX, typename TY, int N, int K, int NBW, int XCAP, int UQ, bool kS1, bool kQuad,
           bool kEp>
 onexn_status launch_plane(PlArgs a, hipStream_t stream) {
-    typedef PlShape<TX, N, K, NBW, XCAP, UQ, WM, kQuad> S;
+    typedef PlShape<TX, N, K, NBW, XCAP, UQ, kQuad> S;
     a.tw = K == 1 ? a.Wo : pl_strip(S::TP, S::XP, S::XITEMS, a, K);
     if (a.tw < 1) return fail(ONEXN_ERR_UNSUPPORTED, "conv2d: the staged tile does not fit");
     const int64_t strips = (a.Wo + a.tw - 1) / a.tw;
     a.tps = int32_t((int64_t(a.rows) * a.tw + S::TP - 1) / S::TP);
-    a.rblocks = (a.R + S::ROWS - 1) / S::ROWS;
+    a.rblocks = (a.R + N - 1) / N;
     const int64_t total = strips * a.tps * a.rblocks;
     if (total < 1 || total > INT32_MAX / kPlThreads)
         return fail(ONEXN_ERR_UNSUPPORTED, "conv2d: grid of %lld workgroups is out of range", (long long)total);
     a.total = int32_t(total);
-    hipLaunchKernelGGL((plane_conv<kDx, TX, TY, N, K, NBW, XCAP, UQ, WM, kS1, kQuad, kEp>), dim3(uint32_t(total)),
+    hipLaunchKernelGGL((plane_conv<kDx, TX, TY, N, K, NBW, XCAP, UQ, kS1, kQuad, kEp>), dim3(uint32_t(total)),
                        dim3(kPlThreads), 0, stream, a);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return fail(ONEXN_ERR_HIP, "conv2d: launch failed: %s", hipGetErrorString(err));
@@ -701,15 +665,14 @@ PlKind pl_kind(const PlArgs& a, int32_t K, int32_t rows) {
     return pl_strip(kPx2, kCap2, 256, a, K) ? kPlStrided : kPlNone;
 }
 
-template <bool kDx, typename TX, typename TY, int N, int WM1, bool kEp>
+template <bool kDx, typename TX, typename TY, int N, bool kEp>
 onexn_status launch_kind(PlKind kind, const PlArgs& p, hipStream_t s) {
-    if (kind == kPlS1) return launch_plane<kDx, TX, TY, N, 3, 2, kCap1, 1, 1, true, true, kEp>(p, s);
-    if (kind == kPlS1Small) return launch_plane<kDx, TX, TY, N, 3, 1, kCapS, 1, 1, true, true, kEp>(p, s);
-    if constexpr (sizeof(TX) == 2) {
-        if constexpr (!kDx)
-            if (kind == kPlStrided) return launch_plane<kDx, TX, TY, N, 3, 1, kCap2, 2, 1, false, true, kEp>(p, s);
-        if (kind == kPlPointQuad) return launch_plane<kDx, TX, TY, N, 1, 2, 1, 1, WM1, true, true, kEp>(p, s);
-        if (kind == kPlPoint) return launch_plane<kDx, TX, TY, N, 1, 2, 1, 1, WM1, kDx, false, kEp>(p, s);
+    if (kind == kPlS1) return launch_plane<kDx, TX, TY, N, 3, 2, kCap1, 1, true, true, kEp>(p, s);
+    if (kind == kPlS1Small) return launch_plane<kDx, TX, TY, N, 3, 1, kCapS, 1, true, true, kEp>(p, s);
+    if constexpr (sizeof(TX) == 2 && !kDx) {
+        if (kind == kPlStrided) return launch_plane<kDx, TX, TY, N, 3, 1, kCap2, 2, false, true, kEp>(p, s);
+        if (kind == kPlPointQuad) return launch_plane<kDx, TX, TY, N, 1, 2, 1, 1, true, true, kEp>(p, s);
+        if (kind == kPlPoint) return launch_plane<kDx, TX, TY, N, 1, 2, 1, 1, false, false, kEp>(p, s);
     }
     return fail(ONEXN_ERR_UNSUPPORTED, "conv2d: no instance for this layer");
 }
@@ -751,6 +714,7 @@ PlArgs pl_fwd_args(const ConvArgs& a) {
     p.s = a.sh;
     p.ph = a.ph;
     p.pw = a.pw;
+    p.dil = 1;
     p.rows = batch * a.Ho;
     return p;
 }
@@ -766,6 +730,7 @@ PlArgs pl_dx_args(const ConvArgs& a, int32_t batch, const void* dy, void* dx) {
     p.Ho = a.H;
     p.Wo = a.W;
     p.s = 1;
+    p.dil = a.sh;
     p.ph = a.kh - 1 - a.ph;
     p.pw = a.kw - 1 - a.pw;
     p.rows = batch * a.H;
@@ -814,8 +779,8 @@ onexn_status launch_planes_fwd(const ConvArgs& a, onexn_dtype xdt, onexn_dtype y
     return with_epilogue(a, [&](auto ep) {
         constexpr bool E = decltype(ep)::value;
         auto by_n = [&](auto tx, auto ty) {
-            if (a.N == 32) return launch_kind<false, decltype(tx), decltype(ty), 32, 1, E>(kind, p, s);
-            return launch_kind<false, decltype(tx), decltype(ty), 16, 1, E>(kind, p, s);
+            if (a.N == 32) return launch_kind<false, decltype(tx), decltype(ty), 32, E>(kind, p, s);
+            return launch_kind<false, decltype(tx), decltype(ty), 16, E>(kind, p, s);
         };
         if (xdt == ONEXN_F32) return by_n(float{}, float{});
         if (ydt == ONEXN_BF16) return by_n(uint16_t{}, uint16_t{});
@@ -824,21 +789,19 @@ onexn_status launch_planes_fwd(const ConvArgs& a, onexn_dtype xdt, onexn_dtype y
 }
 
 bool planes_dx_applies(const ConvArgs& a, onexn_dtype wdt, int32_t batch) {
-    if (a.N < 8 || a.kh != a.kw || (a.kh != 1 && a.kh != 3) || a.sh != 1 || a.sw != 1) return false;
+    if (a.N < 8 || a.kh != 3 || a.kw != 3 || a.sh != a.sw || (wdt == ONEXN_F32 && a.sh != 1)) return false;
     const int es = wdt == ONEXN_F32 ? 4 : 2;
     if (!pl_fits(a, batch, int64_t(a.n) * a.HWo, es, int64_t(batch) * a.H * (a.W + 8))) return false;
-    if (a.kh == 1 && (wdt == ONEXN_F32 || reinterpret_cast<uintptr_t>(a.D) % 16 != 0)) return false;
-    if (a.G * (a.kh == 1 ? 4 : 1) > pl_max_runs(a.kh)) return false;
-    return pl_kind(pl_dx_args(a, batch, nullptr, nullptr), a.kh, 32) != kPlNone;
+    return a.G <= kPlMaxRuns && pl_kind(pl_dx_args(a, batch, nullptr, nullptr), 3, 32) != kPlNone;
 }
 
 onexn_status launch_planes_dx(const ConvArgs& a, onexn_dtype wdt, onexn_dtype dxdt, int32_t batch, const void* dy,
                               void* dx, hipStream_t s) {
     const PlArgs p = pl_dx_args(a, batch, dy, dx);
-    const PlKind kind = pl_kind(p, a.kh, 32);
-    if (wdt == ONEXN_F32) return launch_kind<true, float, float, 32, 4, false>(kind, p, s);
-    if (dxdt == ONEXN_BF16) return launch_kind<true, uint16_t, uint16_t, 32, 4, false>(kind, p, s);
-    return launch_kind<true, uint16_t, float, 32, 4, false>(kind, p, s);
+    const PlKind kind = pl_kind(p, 3, 32);
+    if (wdt == ONEXN_F32) return launch_kind<true, float, float, 32, false>(kind, p, s);
+    if (dxdt == ONEXN_BF16) return launch_kind<true, uint16_t, uint16_t, 32, false>(kind, p, s);
+    return launch_kind<true, uint16_t, float, 32, false>(kind, p, s);
 }
 
 }  // namespace onexn

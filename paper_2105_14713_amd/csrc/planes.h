@@ -112,6 +112,27 @@ struct PlaneAcc {
     }
 };
 
+// First entry of a col-group's [zb, ze) with I >= c0 (I ascends; ze if none).
+__device__ __forceinline__ int32_t lower_entry(const int32_t* __restrict__ I, int32_t zb, int32_t ze, int32_t c0) {
+    int32_t lo = zb, hi = ze;
+    while (hi - lo > 16) {                               // 16 independent samples a round
+        const int32_t step = (hi - lo + 15) / 16;
+        int32_t below = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int32_t e = lo + k * step;
+            below += (e < hi && I[min(e, ze - 1)] < c0) ? 1 : 0;
+        }
+        const int32_t nlo = below == 0 ? lo : lo + (below - 1) * step + 1;
+        hi = below == 0 ? lo : min(hi, lo + below * step);
+        lo = nlo;
+    }
+    int32_t below = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) below += (lo + k < hi && I[min(lo + k, ze - 1)] < c0) ? 1 : 0;
+    return lo + below;
+}
+
 __device__ __forceinline__ bool not_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; }
 
 }  // namespace onexn

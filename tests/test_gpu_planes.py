@@ -61,8 +61,13 @@ BWD = [  # (n, m, k, stride, pad, B, H, W, N)
     (80, 45, 1, 1, 0, 3, 7, 9, 32),
     (140, 270, 1, 1, 0, 2, 8, 8, 16),
     (64, 33, 1, 1, 1, 2, 6, 5, 8),
-    (48, 40, 3, 2, 1, 2, 11, 17, 16),    # weight gradient only: strided octets
+    (48, 40, 3, 2, 1, 2, 11, 17, 16),    # strided: dY spread in the tile, strided octets of X
+    (72, 35, 3, 2, 0, 3, 14, 14, 32),
+    (40, 33, 3, 3, 2, 1, 17, 90, 8),
     (32, 70, 1, 2, 0, 2, 13, 9, 32),
+    (24, 200, 1, 3, 1, 2, 12, 13, 8),
+    (136, 64, 1, 1, 0, 3, 12, 12, 8),    # 1x1 in bf16: 64 and 128 input channels per tile
+    (300, 130, 1, 1, 0, 1, 10, 26, 32),
     (32, 5, 5, 1, 2, 1, 11, 23, 16),
     (32, 3, 7, 3, 3, 2, 25, 26, 32),
     (32, 600, 1, 1, 0, 40, 5, 5, 32),    # several chunks of 512 pixels
