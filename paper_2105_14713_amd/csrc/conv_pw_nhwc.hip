@@ -165,6 +165,22 @@ __global__ void __launch_bounds__(kNThreads) __attribute__((amdgpu_waves_per_eu(
     const bool v4 = (a.n & 3) == 0 && (reinterpret_cast<uintptr_t>(a.y) & 15) == 0;
     const int32_t o = ob + M::row(lane, 0);       // the lane's 4 output channels o .. o+3
 
+    // The lane's epilogue parameters, read once: its output channels are the
+    // same in every column block (read at each store, behind stores that might
+    // have changed them, 96 -> 576 at 14x14, batch 128 took 44.8 us, not 34.6).
+    float es[kEp ? 4 : 1], eb[kEp ? 4 : 1];
+    if constexpr (kEp) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            es[q] = a.ep_scale && o + q < a.n ? a.ep_scale[o + q] : 1.f;
+            eb[q] = a.ep_bias && o + q < a.n ? a.ep_bias[o + q] : 0.f;
+        }
+    }
+    auto finish = [&](int q, float v) __attribute__((always_inline)) {
+        if constexpr (kEp) return epilogue_act(a, fmaf(v, es[q], eb[q]));
+        else return v;
+    };
+
     // MFMA (row, col) of column block b -> output channel ob + row, pixel
     // p0 + b*COLS + col.
     auto store = [&](int32_t b, const acc_t& acc) __attribute__((always_inline)) {
@@ -174,12 +190,12 @@ __global__ void __launch_bounds__(kNThreads) __attribute__((amdgpu_waves_per_eu(
         if (v4 && o + 3 < a.n) {
             f32x4 r;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) r[q] = epilogue<kEp>(a, o + q, acc[q]);
+            for (int q = 0; q < 4; ++q) r[q] = finish(q, acc[q]);
             store_out(reinterpret_cast<f32x4*>(yp), r);
         } else {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if (o + q < a.n) store_out(yp + q, epilogue<kEp>(a, o + q, acc[q]));
+                if (o + q < a.n) store_out(yp + q, finish(q, acc[q]));
         }
     };
     // A pass: NB column blocks b0 + j*wpg (NB independent accumulators).
@@ -323,7 +339,11 @@ onexn_status launch_h(ConvArgs a, hipStream_t s) {
     // Column blocks per tile: two passes of kNBk blocks per wave, fewer where
     // the tile LDS or two workgroups per CU do not allow it.
     const int64_t fit = kNTileLds / nhwc_tile_bytes(kNCols, a.m);
-    int64_t T = std::min<int64_t>({int64_t(kNMaxBlocks), fit, 2 * kNBk * wpg});
+    // Layers with many tiles take four passes: 24 -> 144 at 56x56, batch 128
+    // (1568 tiles of 16 blocks, two sets of slices): 89 us against 115 with 8
+    // blocks; 32 -> 192 at 28x28 (392 tiles of 16): 31 against 27.
+    const int64_t passes = wpg == 1 && blocks * nsets >= 4 * kNBk * 8 * cus ? 4 : 2;
+    int64_t T = std::min<int64_t>({int64_t(kNMaxBlocks), fit, passes * kNBk * wpg});
     T = std::max<int64_t>(1, std::min<int64_t>(T, blocks * nsets / (2 * cus)));
     if (tuning(kTuneNhwcTile) >= 1)   // (at most what fits the CU's LDS)
         T = std::max<int64_t>(1, std::min<int64_t>(tuning(kTuneNhwcTile),
