@@ -20,9 +20,10 @@
 // is computed once.
 //
 // Work split.  A unit is (col-group, NB column blocks of pixels).  A
-// workgroup of four waves takes 4 / KSPLIT units; KSPLIT waves share a unit's
-// kept blocks (contiguous ranges) and add their partial sums through LDS at
-// the end, for layers with few pixels and long col-groups.
+// workgroup of four waves (eight at KSPLIT = 8) takes 4 / KSPLIT units (one);
+// KSPLIT waves share a unit's kept blocks (contiguous ranges) and add their
+// partial sums through LDS at the end, for layers with few pixels and long
+// col-groups.
 //
 // Pipelining.  Steps are taken in batches of kDB: channel indices come in
 // lane-parallel windows of 64 entries loaded a window ahead, a batch's
@@ -37,20 +38,21 @@
 namespace onexn {
 namespace {
 
-constexpr int kDThreads = 256;
+// Waves of a workgroup: four, or the KSPLIT that share one unit.
+constexpr int direct_waves(int ksplit) { return ksplit > 4 ? ksplit : 4; }
 // kDB: MFMA steps per batch (8 for long contractions, 2 for short ones,
 // whose waves would otherwise multiply mostly zero padding).
 template <int N, int NB, int KSPLIT, int kDB, bool kEp>
-__global__ void __launch_bounds__(kDThreads) pw_direct(ConvArgs a) {
+__global__ void __launch_bounds__(64 * direct_waves(KSPLIT)) pw_direct(ConvArgs a) {
     typedef PwMfma<N> M;
     typedef typename M::acc_t acc_t;
     constexpr int KS = M::KS, COLS = M::COLS;
-    constexpr int UPW = 4 / KSPLIT;                 // units per workgroup
-    constexpr int RED = KSPLIT > 1 ? 4 * NB * M::ACC * 64 : 1;
+    constexpr int WAVES = direct_waves(KSPLIT), UPW = WAVES / KSPLIT;   // units per workgroup
+    constexpr int RED = KSPLIT > 1 ? WAVES * NB * M::ACC * 64 : 1;
     __shared__ float sR[RED];
     // Fused epilogue: scale and bias of each unit's N channels, staged when
     // the unit starts and read back run by run at the store.
-    __shared__ __attribute__((aligned(16))) float sEp[kEp ? 4 * 2 * N : 4];
+    __shared__ __attribute__((aligned(16))) float sEp[kEp ? UPW * 2 * N : 4];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -183,6 +185,22 @@ __global__ void __launch_bounds__(kDThreads) pw_direct(ConvArgs a) {
 #pragma unroll
             for (int r = 0; r < M::ACC; ++r) sR[((wave * NB + nb) * M::ACC + r) * 64 + lane] = acc[nb][r];
         __syncthreads();
+        if constexpr (KSPLIT > 4) {
+            // Each wave adds and stores its share of the rows (one wave would
+            // read KSPLIT x 16 values one after another).
+            static_assert(NB == 1, "one column block");
+            float* __restrict__ y = static_cast<float*>(a.y);
+#pragma unroll
+            for (int r = kq; r < M::ACC; r += KSPLIT) {
+                float v = 0.f;
+#pragma unroll
+                for (int k = 0; k < KSPLIT; ++k) v += sR[(k * M::ACC + r) * 64 + lane];
+                const int32_t row = M::row(lane, r), oc = g * N + row;
+                if constexpr (kEp) v = epilogue_act(a, fmaf(v, sEp[row], sEp[N + row]));
+                if (yo[0] >= 0 && oc < a.n) store_out(&y[yo[0] + int64_t(oc) * a.y_c], v);
+            }
+            return;
+        }
         if (kq != 0) return;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
@@ -229,7 +247,8 @@ template <int N, int NB, int KSPLIT>
 onexn_status launch_cfg(ConvArgs a, hipStream_t s) {
     constexpr int COLS = PwMfma<N>::COLS, KS = PwMfma<N>::KS;
     const int64_t units = (int64_t(a.npix) + NB * COLS - 1) / (NB * COLS) * a.G;
-    const int64_t upw = 4 / KSPLIT;
+    constexpr int WAVES = direct_waves(KSPLIT);
+    const int64_t upw = WAVES / KSPLIT;
     const int64_t grid = (units + upw - 1) / upw;
     // A wave's entries run in whole pairs of batches: short shares take
     // small batches.
@@ -238,8 +257,8 @@ onexn_status launch_cfg(ConvArgs a, hipStream_t s) {
     if (tuning(kTuneDirectKdb) >= 0) kdb = tuning(kTuneDirectKdb);
     return with_epilogue(a, [&](auto ep) {
         constexpr bool E = decltype(ep)::value;
-        if (kdb == 2) return launch_grid(pw_direct<N, NB, KSPLIT, 2, E>, a, grid, s, kDThreads);
-        return launch_grid(pw_direct<N, NB, KSPLIT, 8, E>, a, grid, s, kDThreads);
+        if (kdb == 2) return launch_grid(pw_direct<N, NB, KSPLIT, 2, E>, a, grid, s, 64 * WAVES);
+        return launch_grid(pw_direct<N, NB, KSPLIT, 8, E>, a, grid, s, 64 * WAVES);
     });
 }
 
@@ -271,10 +290,22 @@ onexn_status launch_n(ConvArgs a, hipStream_t s) {
         else if (wgs(1, 2) >= want || avg_kept < 256) choice = 3;
         else choice = 4;
     }
+    // Fewer units than two per compute unit at N = 32: eight waves share one.
+    // 512 -> 2048 at 7x7, batch 1 (128 units): 5.4 us against 7.7; 1024 -> 256
+    // at 14x14: batch 1 (56) 6.7 against 7.8, batch 8 (392) 10.1 against 11.1;
+    // 512 -> 128 at 28x28, batch 16 (1568): 17.4 against 16.2.  (At N = 16 a
+    // share is half as long, and eight are no faster than four.)  One-pixel
+    // images (FC rows), whose loads touch a cache line per lane, only below
+    // one unit per compute unit: 1024 -> 300, batch 512 (160 units) 13.1
+    // against 14.7; 2048 -> 1000, batch 256 (256) 23.5 against 22.5.
+    const int64_t units = (int64_t(a.npix) + COLS - 1) / COLS * a.G, cus = device_cu_count();
+    if (tuning(kTuneDirectTile) < 0 && N == 32 && avg_kept >= 128 && (a.HWo > 1 ? units <= 2 * cus : units < cus))
+        choice = 5;
     switch (choice) {
         case 1: return launch_cfg<N, 2, 1>(a, s);
         case 2: return launch_cfg<N, 1, 1>(a, s);
         case 3: return launch_cfg<N, 1, 2>(a, s);
+        case 5: return launch_cfg<N, 1, 8>(a, s);
         default: return launch_cfg<N, 1, 4>(a, s);
     }
 }

@@ -26,7 +26,7 @@ enum Tune : int {
     kTunePwbGp,        // register-gathered bf16: pixels per granule (4, 8)
     kTunePwbRp,        // register-gathered bf16: steps in flight
     kTuneDirectKdb,    // register-operand 1x1: MFMA steps per batch (2, 8)
-    kTuneDirectTile,   // register-operand 1x1: tile shape 1-4
+    kTuneDirectTile,   // register-operand 1x1: tile shape 1-5
     kTuneFmaTpw,       // 1x1 FMA: pixel tiles per workgroup
     kTuneFmaNoV4,      // 1x1 FMA: 1 disables 16-byte pixel quads
     kTuneFmaTile,      // 1x1 FMA: tile shape 1-5
