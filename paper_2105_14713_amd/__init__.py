@@ -113,12 +113,20 @@ def _check(status: int, where: str):
         raise OnexnError(status, where, last_error())
 
 
+_DTYPE_CODES = {torch.float32: F32, torch.bfloat16: BF16}
+
+
 def _dtype_code(dt: torch.dtype) -> int:
-    if dt == torch.float32:
-        return F32
-    if dt == torch.bfloat16:
-        return BF16
-    raise TypeError(f"unsupported dtype {dt}; expected float32 or bfloat16")
+    code = _DTYPE_CODES.get(dt)
+    if code is None:
+        raise TypeError(f"unsupported dtype {dt}; expected float32 or bfloat16")
+    return code
+
+
+def _current_stream(t: torch.Tensor) -> int:
+    """torch's current stream on t's device.  The raw lookup costs 0.1 us, the
+    one through a Stream object 1.8, of a call's @T@."""
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
 def _host_weight(w: torch.Tensor) -> torch.Tensor:
@@ -168,7 +176,7 @@ def build_mask_dev(w: torch.Tensor, N: int, p: float, rearrange: bool,
     mask = torch.empty((m, G), dtype=torch.uint8, device=w.device)
     t = ctypes.c_int64(0)
     if stream is None:
-        stream = torch.cuda.current_stream(w.device).cuda_stream
+        stream = _current_stream(w)
     st = load_library().onexn_build_mask_dev(w.data_ptr(), _dtype_code(w.dtype), n, m, kh, kw, int(N),
                                              float(p), int(bool(rearrange)), perm.data_ptr(),
                                              mask.data_ptr(), ctypes.addressof(t), workspace.data_ptr(),
@@ -201,15 +209,17 @@ def out_hw(H: int, W: int, kh: int, kw: int, stride, pad) -> Tuple[int, int]:
 
 
 def _pair(v):
-    return (int(v), int(v)) if isinstance(v, int) else (int(v[0]), int(v[1]))
+    return (v, v) if type(v) is int else (int(v), int(v)) if isinstance(v, int) else (int(v[0]), int(v[1]))
 
 
 def _epilogue_args(n, scale, bias, act):
     """(scale ptr, bias ptr, act code, fused?) for the fused entry point."""
+    if scale is None and bias is None and act == "none":
+        return 0, 0, 0, False
     if act not in ACTS:
         raise ValueError(f"act must be one of {sorted(ACTS)}")
     for name, v in (("scale", scale), ("bias", bias)):
-        if v is not None and (v.device.type != "cuda" or v.dtype != torch.float32 or
+        if v is not None and (not v.is_cuda or v.dtype != torch.float32 or
                               not v.is_contiguous() or v.numel() != n):
             raise ValueError(f"{name} must be a contiguous float32 device tensor of {n} entries")
     fused = scale is not None or bias is not None or act != "none"
@@ -217,39 +227,44 @@ def _epilogue_args(n, scale, bias, act):
             ACTS[act], fused)
 
 
+_LAYOUTS = {"nchw": NCHW, "nhwc": NHWC}
+
+
 def _conv_call(P, I, D, n, x, stride, pad, layout, out_dtype, out, stream, scale, bias, act):
     """Validates a conv2d_fwd call and marshals its arguments: returns (library
     function, argument tuple, out).  Nothing is launched."""
-    for name, tns in (("P", P), ("I", I), ("D", D), ("x", x)):
-        if tns.device.type != "cuda":
-            raise ValueError(f"{name} must be a device tensor (the convolution only runs on the GPU)")
-        if not tns.is_contiguous():
+    for tns in (P, I, D, x):
+        if not (tns.is_cuda and tns.is_contiguous()):
+            name = "PIDx"[[tns is v for v in (P, I, D, x)].index(True)]
+            if not tns.is_cuda:
+                raise ValueError(f"{name} must be a device tensor (the convolution only runs on the GPU)")
             raise ValueError(f"{name} must be contiguous")
     if D.dim() != 4:
         raise ValueError("D must be [t][N][kh][kw]")
     t, N, kh, kw = D.shape
     if t != I.numel():
         raise ValueError("D and I disagree on t")
-    lay = {"nchw": NCHW, "nhwc": NHWC}[layout]
+    lay = _LAYOUTS[layout]
     if lay == NCHW:
         B, m, H, W = x.shape
     else:
         B, H, W, m = x.shape
-    stride, pad = _pair(stride), _pair(pad)
-    Ho, Wo = out_hw(H, W, kh, kw, stride, pad)
+    sh, sw = _pair(stride)
+    ph, pw = _pair(pad)
+    Ho, Wo = (H + 2 * ph - kh) // sh + 1, (W + 2 * pw - kw) // sw + 1
     odt = x.dtype if out_dtype is None else out_dtype
     shape = (B, n, Ho, Wo) if lay == NCHW else (B, Ho, Wo, n)
     if out is None:
-        out = torch.empty(shape, dtype=odt, device=x.device)
+        out = x.new_empty(shape, dtype=odt)
     elif tuple(out.shape) != shape or out.dtype != odt or not out.is_contiguous():
         raise ValueError("out has the wrong shape, dtype or layout")
     if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
+        stream = _current_stream(x)
     sp, bp, ac, fused = _epilogue_args(int(n), scale, bias, act)
     args = (P.data_ptr(), I.data_ptr() if t else 0, D.data_ptr() if t else 0, _dtype_code(D.dtype),
-            int(n), m, kh, kw, N, t, x.data_ptr(), _dtype_code(x.dtype), lay, B, H, W, stride[0],
-            stride[1], pad[0], pad[1], out.data_ptr(), _dtype_code(odt))
-    lib = load_library()
+            int(n), m, kh, kw, N, t, x.data_ptr(), _dtype_code(x.dtype), lay, B, H, W, sh, sw, ph, pw,
+            out.data_ptr(), _dtype_code(odt))
+    lib = _lib or load_library()
     if fused:
         return lib.onexn_conv2d_fwd_fused, args + (sp, bp, ac, stream), out
     return lib.onexn_conv2d_fwd, args + (stream,), out
@@ -266,13 +281,15 @@ def conv2d_fwd(P: torch.Tensor, I: torch.Tensor, D: torch.Tensor, n: int, x: tor
     ("relu", "relu6") it calls ``onexn_conv2d_fwd_fused``: y = act(scale * acc + bias)."""
     fn, args, out = _conv_call(P, I, D, n, x, stride, pad, layout, out_dtype, out, stream, scale,
                                bias, act)
-    _check(fn(*args), fn.__name__)
+    st = fn(*args)
+    if st != ONEXN_OK:
+        _check(st, fn.__name__)
     return out
 
 
 def _dev_contig(**tensors):
     for name, tns in tensors.items():
-        if tns.device.type != "cuda" or not tns.is_contiguous():
+        if not (tns.is_cuda and tns.is_contiguous()):
             raise ValueError(f"{name} must be a contiguous device tensor")
 
 
@@ -290,11 +307,11 @@ def conv2d_bwd_data(P, I, D, n: int, m: int, dy: torch.Tensor, input_hw, stride=
         raise ValueError("dy does not have the layer's output shape")
     odt = dy.dtype if out_dtype is None else out_dtype
     if out is None:
-        out = torch.empty((B, m, H, W), dtype=odt, device=dy.device)
+        out = dy.new_empty((B, m, H, W), dtype=odt)
     elif tuple(out.shape) != (B, m, H, W) or out.dtype != odt or not out.is_contiguous():
         raise ValueError("out has the wrong shape, dtype or layout")
     if stream is None:
-        stream = torch.cuda.current_stream(dy.device).cuda_stream
+        stream = _current_stream(dy)
     st = load_library().onexn_conv2d_bwd_data(
         P.data_ptr(), I.data_ptr() if t else 0, D.data_ptr() if t else 0, _dtype_code(D.dtype), int(n),
         int(m), kh, kw, N, t, dy.data_ptr(), _dtype_code(dy.dtype), B, H, W, stride[0], stride[1],
@@ -316,11 +333,11 @@ def conv2d_bwd_weight(P, I, n: int, N: int, kernel_hw, x: torch.Tensor, dy: torc
     if tuple(dy.shape) != (B, n) + out_hw(H, W, kh, kw, stride, pad) or dy.dtype != x.dtype:
         raise ValueError("dy does not have the layer's output shape or x's dtype")
     if out is None:
-        out = torch.empty((t, N, kh, kw), dtype=torch.float32, device=x.device)
+        out = x.new_empty((t, N, kh, kw), dtype=torch.float32)
     elif tuple(out.shape) != (t, N, kh, kw) or out.dtype != torch.float32 or not out.is_contiguous():
         raise ValueError("out must be a contiguous fp32 tensor [t][N][kh][kw]")
     if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
+        stream = _current_stream(x)
     st = load_library().onexn_conv2d_bwd_weight(
         P.data_ptr(), I.data_ptr() if t else 0, int(n), m, kh, kw, int(N), t, x.data_ptr(),
         _dtype_code(x.dtype), dy.data_ptr(), B, H, W, stride[0], stride[1], pad[0], pad[1],
@@ -338,7 +355,7 @@ def fc_fwd(P: torch.Tensor, I: torch.Tensor, D: torch.Tensor, n: int, x: torch.T
     ("cols", one row per feature); returns y [B][n] or [n][B] (rearranged
     feature order).  D is [t][N] or [t][N][1][1]."""
     for name, tns in (("P", P), ("I", I), ("D", D), ("x", x)):
-        if tns.device.type != "cuda":
+        if not tns.is_cuda:
             raise ValueError(f"{name} must be a device tensor")
         if not tns.is_contiguous():
             raise ValueError(f"{name} must be contiguous")
@@ -352,11 +369,11 @@ def fc_fwd(P: torch.Tensor, I: torch.Tensor, D: torch.Tensor, n: int, x: torch.T
     odt = x.dtype if out_dtype is None else out_dtype
     shape = (B, n) if layout == "rows" else (n, B)
     if out is None:
-        out = torch.empty(shape, dtype=odt, device=x.device)
+        out = x.new_empty(shape, dtype=odt)
     elif tuple(out.shape) != shape or out.dtype != odt or not out.is_contiguous():
         raise ValueError("out has the wrong shape, dtype or layout")
     if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
+        stream = _current_stream(x)
     sp, bp, ac, _ = _epilogue_args(int(n), scale, bias, act)
     st = load_library().onexn_fc_fwd(P.data_ptr(), I.data_ptr() if t else 0, D.data_ptr() if t else 0,
                                      _dtype_code(D.dtype), int(n), int(m), N, t, x.data_ptr(),
