@@ -7,8 +7,8 @@
 // per col-group a contraction over the output pixels of its N rows of dY with
 // one row of X per (kept block, tap) pair, pairs numbered tap-major.
 //
-// Work.  A workgroup computes the entries of 32 pairs of one col-group (N x
-// 32).  The contraction runs along the pixels, which are contiguous in both
+// Work.  A workgroup computes the entries of 32 pairs and R rows of one
+// col-group (R = N, or half of N = 32 for layers of few tiles).  The contraction runs along the pixels, which are contiguous in both
 // operands, so a fragment entry is eight neighbouring pixels of a row: a lane
 // loads eight with one 16-byte load and stores them to LDS as they are;
 // nothing is transposed.  Octets are cut per output row (a 1x1 layer without
@@ -63,13 +63,14 @@ constexpr int kDwPairs = 32;         // pairs of a tile
 constexpr int kDwOcts = 64;          // octets of a chunk: one per lane, so a wave stages one row at a time
 constexpr int kDwRS = kDwThreads / kDwOcts;   // rows staged per item
 
-template <int N> struct DwShape {
-    static constexpr int RP = kDwPairs + N + 1;          // odd
-    static constexpr int UX = kDwPairs / kDwRS, UY = N / kDwRS;
+// R: rows of dY of a workgroup (16 or 32).
+template <int R> struct DwShape {
+    static constexpr int RP = kDwPairs + R + 1;          // odd
+    static constexpr int UX = kDwPairs / kDwRS, UY = R / kDwRS;
     static constexpr int OPW = kDwOcts / kDwWaves;       // octets a wave multiplies per chunk
-    static constexpr int KG = N == 32 ? 2 : 4;           // octets of one MFMA
+    static constexpr int KG = R == 32 ? 2 : 4;           // octets of one MFMA
     static constexpr int STEPS = OPW / KG;
-    static_assert(kDwOcts * RP * 16 >= kDwWaves * kDwPairs * N * 4, "the partial sums fit the staging space");
+    static_assert(kDwOcts * RP * 16 >= kDwWaves * kDwPairs * R * 4, "the partial sums fit the staging space");
 };
 
 // Eight values between load and store: as loaded, or element by element.
@@ -110,10 +111,10 @@ __device__ __forceinline__ u32x4 masked(const uint32_t (&v)[8], uint32_t m) {
     return p;
 }
 
-template <int N, int MODE>
+template <int N, int R, int MODE>
 __global__ void __launch_bounds__(kDwThreads, 4) bwd_weight_bf16(DwArgs a) {
-    typedef DwShape<N> S;
-    typedef PlaneMfma<N> M;
+    typedef DwShape<R> S;
+    typedef PlaneMfma<R> M;
     constexpr int NB = kDwPairs / M::COLS;               // column blocks of a tile's pairs
     typedef Oct<MODE != kStrided> XOct;
     typedef Oct<true> YOct;
@@ -123,7 +124,8 @@ __global__ void __launch_bounds__(kDwThreads, 4) bwd_weight_bf16(DwArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Consecutive ids: the tiles of one col-group (one L2).
     const int32_t L = xcd_remap(int32_t(blockIdx.x), a.total);
-    const int32_t tile = L % a.tiles, g = L / a.tiles;
+    const int32_t tile = L % a.tiles, rowset = L / a.tiles;
+    const int32_t g = rowset / (N / R), r0 = (rowset - g * (N / R)) * R;   // col-group, its first row here
     const int32_t zb = max(0, min(a.P[g], a.t)), cnt = max(zb, min(a.P[g + 1], a.t)) - zb;
     const int32_t pairs = cnt * a.KK, pr0 = tile * kDwPairs;
     if (pr0 >= pairs) return;                            // (uniform: before any barrier)
@@ -161,11 +163,11 @@ __global__ void __launch_bounds__(kDwThreads, 4) bwd_weight_bf16(DwArgs a) {
         const bool in = b < a.batch;
         const int32_t left = a.Wo - 8 * k;               // columns of the row from this octet on
         ym[s] = in ? (left >= 8 ? 255u : (1u << left) - 1) : 0u;
-        const int32_t yb = int32_t(uint32_t(b * a.n + g * N) * uint32_t(HWo)) + oh * a.Wo + 8 * k;
+        const int32_t yb = int32_t(uint32_t(b * a.n + g * N + r0) * uint32_t(HWo)) + oh * a.Wo + 8 * k;
 #pragma unroll
         for (int u = 0; u < S::UY; ++u) {
             const int32_t row = srow + kDwRS * u;
-            const bool ok = in && row < N && g * N + row < a.n;
+            const bool ok = in && g * N + r0 + row < a.n;
             const int32_t at = ok ? yb + row * HWo : 0;
             ye[s][u] = ok && at > a.y_total - 8 ? at : -1;
             if (!ok) ye[s][u] = -2;                      // no such row: zeros
@@ -225,7 +227,7 @@ __global__ void __launch_bounds__(kDwThreads, 4) bwd_weight_bf16(DwArgs a) {
 
     // ---- Compute roles: each wave takes OPW octets of a chunk.
     const int kg = lane / M::COLS, col = lane % M::COLS;
-    PlaneAcc<N, 1> acc[NB];
+    PlaneAcc<R, 1> acc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb].zero();
     const u32x4* const lb = sU + (wave * S::OPW + kg) * S::RP + col;
@@ -299,11 +301,11 @@ __global__ void __launch_bounds__(kDwThreads, 4) bwd_weight_bf16(DwArgs a) {
         float v = 0.f;
 #pragma unroll
         for (int j = 0; j < kDwWaves; ++j) v += part[j * E + e];
-        finish(M::row(l, nr % M::ACC), pr0 + (nr / M::ACC) * M::COLS + l % M::COLS, v);
+        finish(r0 + M::row(l, nr % M::ACC), pr0 + (nr / M::ACC) * M::COLS + l % M::COLS, v);
     }
 }
 
-template <int N, int MODE>
+template <int N, int R, int MODE>
 onexn_status launch_dw(DwArgs d, hipStream_t s) {
     const int64_t octs = int64_t(d.batch) * d.Ho * d.noct;
     d.chunks = int32_t((octs + kDwOcts - 1) / kDwOcts);
@@ -312,10 +314,10 @@ onexn_status launch_dw(DwArgs d, hipStream_t s) {
     d.drow = kDwOcts / d.noct;
     d.db = d.drow / d.Ho;
     d.doh = d.drow % d.Ho;
-    const int64_t total = int64_t(d.G) * d.tiles;
+    const int64_t total = int64_t(d.G) * (N / R) * d.tiles;
     if (total > INT32_MAX / kDwThreads) return fail(ONEXN_ERR_UNSUPPORTED, "conv2d_bwd_weight: grid out of range");
     d.total = int32_t(total);
-    hipLaunchKernelGGL((bwd_weight_bf16<N, MODE>), dim3(uint32_t(total)), dim3(kDwThreads), 0, s, d);
+    hipLaunchKernelGGL((bwd_weight_bf16<N, R, MODE>), dim3(uint32_t(total)), dim3(kDwThreads), 0, s, d);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return fail(ONEXN_ERR_HIP, "conv2d_bwd_weight: launch failed: %s", hipGetErrorString(err));
     return ONEXN_OK;
@@ -367,7 +369,14 @@ onexn_status launch_bwd_weight_bf16(const ConvArgs& a, int32_t batch, const void
     d.y_total = batch * a.n * a.HWo;
     auto by_mode = [&](auto MODE) {
         constexpr int m = decltype(MODE)::value;
-        return a.N == 32 ? launch_dw<32, m>(d, s) : launch_dw<16, m>(d, s);
+        if (a.N == 16) return launch_dw<16, 16, m>(d, s);
+        // Half the rows per workgroup where the halves still fit three
+        // quarters of the compute units (a workgroup fills one): 256 -> 512 1x1
+        // at 28x28, batch 32 (72 tiles) 57 us against 68; 256 -> 128 at 14x14,
+        // batch 64 (18) 33 against 41; but 1000 -> 200 at 7x7 (112) 27 against
+        // 19 and 256 -> 1024 at 14x14 (144) 65 against 44.
+        const int64_t tiles = (int64_t(a.t) * a.KK + kDwPairs - 1) / kDwPairs + a.G / 2;
+        return 8 * tiles < 3 * int64_t(device_cu_count()) ? launch_dw<32, 16, m>(d, s) : launch_dw<32, 32, m>(d, s);
     };
     if (dw_flat(a)) return by_mode(std::integral_constant<int, kFlat>{});
     if (a.sw == 1) return by_mode(std::integral_constant<int, kTap>{});
