@@ -197,3 +197,37 @@ def test_unknown_activation_is_rejected():
                                     0, y.data_ptr(), 0, None, None, 3, None)
     assert st == 2   # ONEXN_ERR_ARG
     assert "activation" in onexn.last_error()
+
+
+VARIANTS = {  # (k, layout, dtype, n, m, stride, pad, H, W, knobs)
+    "direct_8_waves": (1, "nchw", torch.float32, 75, 700, 1, 0, 7, 9, {"pw_kernel": 3, "direct_tile": 5}),
+    "direct_8_waves_short": (1, "nchw", torch.float32, 75, 33, 2, 1, 11, 10, {"pw_kernel": 3, "direct_tile": 5}),
+    "nhwc_16_blocks": (1, "nhwc", torch.float32, 300, 24, 1, 0, 19, 17, {"nhwc_tile": 16}),
+    "nhwc_16_blocks_streamed": (1, "nhwc", torch.float32, 272, 150, 2, 0, 40, 21, {"nhwc_tile": 16}),
+    "planes_k3_f32": (3, "nchw", torch.float32, 75, 40, 1, 1, 13, 21, {"kernel": 2}),
+    "planes_k3_bf16": (3, "nchw", torch.bfloat16, 75, 40, 2, 1, 13, 21, {"kernel": 2}),
+    "planes_pw_bf16": (1, "nchw", torch.bfloat16, 75, 130, 1, 0, 9, 7, {"kernel": 2}),
+}
+
+
+@pytest.mark.parametrize("N", [16, 32])
+@pytest.mark.parametrize("kind", sorted(VARIANTS))
+def test_kernel_variants_with_and_without_epilogue(kind, N, tune):
+    """Tile and wave counts that small layers do not choose by themselves, with
+    ragged col-groups: exact on integers, plain and with the affine map."""
+    k, layout, dt, n, m, s, pd, H, W, knobs = VARIANTS[kind]
+    for name, v in knobs.items():
+        tune(name, v)
+    w, x = workloads.gen_integer_layer(seed=N + m, cout=n, cin=m, k=k, batch=3, H=H, W=W, wmax=2, xmax=2)
+    scale, bias = _params(n, m)
+    xd = (x if layout == "nchw" else x.permute(0, 2, 3, 1).contiguous()).to(dt).cuda()
+    for p in (0.0, 0.5, 0.95):
+        layer = onexn.prepare_layer(w.to(dt), N, p, True)
+        conv = oracle.conv2d(x.double().numpy(), oracle.prune(w.double().numpy(), N, p, True).wbar,
+                             (s, s), (pd, pd))
+        for kw, ref in (({}, conv),
+                        (dict(scale=scale.cuda(), bias=bias.cuda(), act="relu"),
+                         oracle.epilogue(conv, scale.double().numpy(), bias.double().numpy(), "relu"))):
+            y = layer.forward(xd, s, pd, layout, torch.float32, **kw)
+            y = y if layout == "nchw" else y.permute(0, 3, 1, 2)
+            np.testing.assert_array_equal(y.double().cpu().numpy(), ref)

@@ -106,6 +106,25 @@ def test_bf16_weight_gradient_does_not_vary():
     assert all(np.array_equal(runs[0], r) for r in runs[1:])
 
 
+@pytest.mark.parametrize("k,s,pd", [(1, 1, 0), (3, 1, 1), (1, 2, 0), (3, 2, 1)])
+@pytest.mark.parametrize("n,m,N", [
+    (150, 40, 32),     # few tiles: half the rows of a col-group per workgroup, 22 rows in the last one
+    (170, 1400, 32),   # a 1x1 layer of many tiles: all 32 rows; 10 rows in the last col-group
+    (170, 30, 16),
+])
+def test_bf16_weight_gradient_rows(n, m, N, k, s, pd):
+    if k == 3:
+        m = max(m // 9, 30)
+    w, x = workloads.gen_integer_layer(n + m, n, m, k, 2, 10, 8)
+    Ho, Wo = onexn.out_hw(10, 8, k, k, (s, s), (pd, pd))
+    dy = torch.randint(-3, 4, (2, n, Ho, Wo), generator=torch.Generator().manual_seed(m)).float()
+    for p in (0.0, 0.5):
+        L, _, dD = _grads(w.bfloat16(), x.bfloat16(), dy.bfloat16(), N, p, s, pd)
+        T = oracle.prune(w.double().numpy(), N, p, True).T
+        dw = oracle.conv2d_bwd_weight(x.double().numpy(), dy.double().numpy(), T, N, (k, k), (s, s), (pd, pd))
+        np.testing.assert_array_equal(dD, oracle.pack(dw, T, N)[2])
+
+
 def _norm_err(a, b):
     return np.linalg.norm(a - b) / np.linalg.norm(b)
 
