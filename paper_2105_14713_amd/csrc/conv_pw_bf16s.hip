@@ -48,6 +48,17 @@
 // entry's staged input row, transposed, for each of the tile's four 32-pixel
 // column blocks.  Rows are stored in groups of four followed by 64 bytes of
 // padding, so the rows one transposed read touches spread over the LDS banks.
+//
+// What bounds it: instruction issue and LDS latency, at four waves per SIMD
+// (2048 -> 2048 at 14x14, batch 256, 30 % kept: vector issue 44 % of the
+// cycles, LDS 31 %, matrix pipes 22 %, waves waiting 53 %).  Most of a window's
+// masks are needed only in a col-group's last one and where it spans three
+// chunks, and the reads of a column block came after the products of the one
+// before.  With the masks behind one test (37 -> 26 vector instructions a
+// window) and all ten reads issued before the first product 281 -> 259 us
+// (the reads alone: 272).
+// Taking the short last set's items after all others, for an even finish,
+// reads X from HBM once more: 315 us.
 
 #include "lds_copy.h"
 #include "pw_common.h"
@@ -84,9 +95,6 @@ __device__ __forceinline__ v4i16 tr_read(const lds_char* p) {
 __device__ __forceinline__ bf16x8 join(v4i16 lo, v4i16 hi) {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
-
-// LDS byte offset of ring row R (0 <= R < kSRingRows): R * 256 + (R / 4) * 64.
-__device__ __forceinline__ int32_t ring_row_off(int32_t R) { return (R << 8) + ((R >> 2) << 6); }
 
 template <typename TY, bool kEp>
 __global__ void __launch_bounds__(kSThreads) pw_bf16s(ConvArgs a) {
@@ -168,6 +176,7 @@ __global__ void __launch_bounds__(kSThreads) pw_bf16s(ConvArgs a) {
     // block (A: outputs of the block; B: pixels of a column block).
     const int k1 = 8 * (lane >> 5) + ((lane & 15) >> 2);
     const int colb = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+    const int32_t aat = aoff + k1 * 64 + colb;           // the lane's first weights in the slot
     TY* __restrict__ y = static_cast<TY*>(a.y);
     __syncthreads();   // the first chunk has landed
 
@@ -218,22 +227,28 @@ __global__ void __launch_bounds__(kSThreads) pw_bf16s(ConvArgs a) {
 
         int32_t epoch = 0;   // chunks 0 .. epoch of this item have landed
         auto process = [&](int u, int32_t j) __attribute__((always_inline)) {
-            const int32_t cnt = min(16, it.nE - 16 * j);
-            // First and last entries (entry e sits in lane 4 (e % 4) + 32 (e / 8),
-            // in c2 when e % 8 >= 4); channels clamped into [0, m) for gating.
-            const int32_t el = cnt - 1;
-            const int32_t lanel = 4 * (el & 3) + 32 * (el >> 3);
-            const int32_t lastc = (el & 4) ? __builtin_amdgcn_readlane(c2[u], lanel)
-                                           : __builtin_amdgcn_readlane(c1[u], lanel);
-            const int32_t firstc = __builtin_amdgcn_readlane(c1[u], 0);
-            const int32_t qf = min(max(firstc, 0), a.m - 1) / kSKc;
-            const int32_t ql = min(max(lastc, 0), a.m - 1) / kSKc;
             *reinterpret_cast<i32x4*>(slot + lane * 16) = av[u];
-            const bool ok1 = (k1 < cnt) & (uint32_t(c1[u]) < uint32_t(a.m));
-            const bool ok2 = (k1 + 4 < cnt) & (uint32_t(c2[u]) < uint32_t(a.m));
-            const int32_t xr1 = ring_row_off((c1[u] + it.kbase) & (kSRingRows - 1));
-            const int32_t xr2 = ring_row_off((c2[u] + it.kbase) & (kSRingRows - 1));
-            const int32_t q1 = c1[u] >> 7, q2 = c2[u] >> 7;
+            // Row R = (c + kbase) mod kSRingRows of the lane's entries, read
+            // from byte colb: R * 256 + (R / 4) * 64 = R * 272 - (R % 4) * 16.
+            auto row_at = [&](int32_t c) __attribute__((always_inline)) {
+                const int32_t R = (c + it.kbase) & (kSRingRows - 1);
+                return __mul24(R, 272) + (colb - ((R & 3) << 4));
+            };
+            const int32_t xr1 = row_at(c1[u]), xr2 = row_at(c2[u]);
+            // Chunks of the first and last entries (entry e sits in lane
+            // 4 (e % 4) + 32 (e / 8), in c2 when e % 8 >= 4).
+            const int32_t first = __builtin_amdgcn_readlane(c1[u], 0), last = __builtin_amdgcn_readlane(c2[u], 44);
+            int32_t qf = first >> 7, ql = last >> 7;
+            // Nearly all windows are whole, of channels inside [0, m) and over
+            // at most two chunks: nothing to mask.
+            const int32_t cnt = it.nE - 16 * j;
+            const bool plain = ((cnt - 16) | first | last | (a.m - 1 - last) | (qf + 1 - ql)) >= 0;   // (none negative)
+            if (!plain) {                                // channels clamped into [0, m) for gating
+                const int32_t el = min(16, cnt) - 1, lanel = 4 * (el & 3) + 32 * (el >> 3);
+                const int32_t lastc = __builtin_amdgcn_readlane((el & 4) ? c2[u] : c1[u], lanel);
+                qf = min(max(first, 0), a.m - 1) / kSKc;
+                ql = min(max(lastc, 0), a.m - 1) / kSKc;
+            }
             // Passes over chunks (lo, hi], at most two each, ending at ql.
             int32_t lo = qf - 1;
             while (true) {
@@ -242,17 +257,26 @@ __global__ void __launch_bounds__(kSThreads) pw_bf16s(ConvArgs a) {
                     __syncthreads();
                     ++epoch;
                 }
-                const bool in1 = ok1 & (q1 > lo) & (q1 <= hi), in2 = ok2 & (q2 > lo) & (q2 <= hi);
-                const int32_t xo1 = in1 ? xr1 : kSZeroOff, xo2 = in2 ? xr2 : kSZeroOff;
-                const int32_t ao1 = in1 ? aoff + k1 * 64 : kSZeroOff;
-                const int32_t ao2 = in2 ? aoff + (k1 + 4) * 64 : kSZeroOff;
-                const bf16x8 af = join(tr_read(lx + ao1 + colb), tr_read(lx + ao2 + colb));
+                int32_t xo1 = xr1, xo2 = xr2, ao1 = aat, ao2 = aat + 256;
+                if (!plain) {
+                    int32_t d1 = c1[u], d2 = c2[u];
+                    asm("" : "+v"(d1), "+v"(d2));        // (else the tests are hoisted to every window)
+                    const int32_t q1 = d1 >> 7, q2 = d2 >> 7;
+                    const bool in1 = (k1 < cnt) & (uint32_t(d1) < uint32_t(a.m)) & (q1 > lo) & (q1 <= hi);
+                    const bool in2 = (k1 + 4 < cnt) & (uint32_t(d2) < uint32_t(a.m)) & (q2 > lo) & (q2 <= hi);
+                    xo1 = in1 ? xr1 : kSZeroOff + colb;
+                    xo2 = in2 ? xr2 : kSZeroOff + colb;
+                    ao1 = in1 ? ao1 : kSZeroOff + colb;
+                    ao2 = in2 ? ao2 : kSZeroOff + colb;
+                }
+                const bf16x8 af = join(tr_read(lx + ao1), tr_read(lx + ao2));
                 v4i16 rb[kSBlocks][2];
 #pragma unroll
                 for (int e = 0; e < kSBlocks; ++e) {
-                    rb[e][0] = tr_read(lx + xo1 + colb + 64 * e);
-                    rb[e][1] = tr_read(lx + xo2 + colb + 64 * e);
+                    rb[e][0] = tr_read(lx + xo1 + 64 * e);
+                    rb[e][1] = tr_read(lx + xo2 + 64 * e);
                 }
+                __builtin_amdgcn_sched_barrier(0);       // all reads in flight before the first product
 #pragma unroll
                 for (int e = 0; e < kSBlocks; ++e)
                     acc[e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, join(rb[e][0], rb[e][1]), acc[e], 0, 0, 0);
