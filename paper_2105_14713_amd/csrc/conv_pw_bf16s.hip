@@ -378,6 +378,25 @@ bool pw_bf16s_applies(const ConvArgs& a, onexn_dtype xdt, onexn_dtype ydt, onexn
     return true;
 }
 
+// Whether this kernel is the faster one where the register-gathered kernel
+// fits too: long contractions whose items fill the chip, that is, rounds of
+// items of which the waves with a col-group make up 65 % of the wave slots, or
+// one round (then, below 1024 channels, with half a set of col-groups at least
+// and no second set).  us gathered and staged, p = 0.5, 14x14, batch 64:
+// 1024 -> 256 (one round) 34.3 and 22.7; 512 -> 256 19.9 and 16.5, 512 -> 128
+// 13.7 and 15.0, 512 -> 512 20.6 and 22.4; 1024 -> 4096 (83 % of four rounds)
+// 148 and 127; 1024 -> 1024 (42 % of two) 37.4 and 59.8; batch 160 (69 % of
+// three) 512 -> 1024 56.9 and 52.6, 1024 -> 1024 80.9 and 88.7, 2048 -> 1024
+// 153 and 136.
+bool pw_bf16s_preferred(const ConvArgs& a) {
+    if (a.m < 512) return false;
+    const int64_t tiles = (int64_t(a.npix / a.HWo) * ((a.HWo + 7) / 8) + kSGran - 1) / kSGran;
+    const int64_t cus = device_cu_count(), items = tiles * ((a.G + kSCompute - 1) / kSCompute);
+    const int64_t rounds = (items + cus - 1) / cus;
+    if (rounds == 1) return a.m >= 1024 || (2 * a.G >= kSCompute && a.G <= kSCompute);
+    return 100 * tiles * a.G >= 65 * kSCompute * cus * rounds;
+}
+
 onexn_status launch_pw_bf16s(ConvArgs a, onexn_dtype ydt, hipStream_t s) {
     return with_epilogue(a, [&](auto ep) {
         constexpr bool E = decltype(ep)::value;

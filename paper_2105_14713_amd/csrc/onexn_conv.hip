@@ -125,17 +125,20 @@ onexn_status conv2d_fwd(const int32_t* P_dev, const int32_t* I_dev, const void* 
         a.y_pix = n;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // bf16 1x1 N = 32 layers: the LDS-staged kernel for long contractions
-    // (2048 -> 2048 at 14x14, batch 256: 313 us against 360 us register-
-    // gathered), the register-gathered one otherwise.  The pwb_kernel tuning
-    // forces 1: register-gathered, 2: staged (an error where it does not fit).
+    // bf16 1x1 N = 32 layers: the LDS-staged kernel where it is the faster one
+    // (2048 -> 2048 at 14x14, batch 256: 259 us against 360 us register-
+    // gathered) or the only one, the register-gathered one otherwise.  The
+    // pwb_kernel tuning forces 1: register-gathered, 2: staged (an error where
+    // it does not fit).
     if (!generic_forced()) {
         const int32_t pbk = tuning(kTunePwbKernel);
         const bool staged = pw_bf16s_applies(a, xdt, ydt, layout);
         if (pbk == 2 && !staged)
             return fail(ONEXN_ERR_UNSUPPORTED, "conv2d_fwd: the LDS-staged bf16 kernel does not fit this layer");
-        if (staged && (pbk == 2 || (pbk != 1 && a.m >= 512))) return launch_pw_bf16s(a, ydt, s);
-        if (pw_bf16r_applies(a, xdt, ydt, layout)) return launch_pw_bf16r(a, ydt, s);
+        const bool gathered = pw_bf16r_applies(a, xdt, ydt, layout);
+        if (staged && (pbk == 2 || (pbk != 1 && (pw_bf16s_preferred(a) || (!gathered && a.m >= 512)))))
+            return launch_pw_bf16s(a, ydt, s);
+        if (gathered) return launch_pw_bf16r(a, ydt, s);
     }
     // fp32 1x1 layers: the resident-tile kernel for stride-1 layers that
     // widen the channels over many pixels, the register-operand kernel for
