@@ -56,6 +56,7 @@
 
 #include "lds_copy.h"
 #include "planes.h"
+#include "tile_div.h"
 
 namespace onexn {
 namespace {
@@ -144,10 +145,6 @@ __device__ __forceinline__ void for_each_index(F&& f) {
     for_each_index_impl(f, std::make_integer_sequence<int, Count>{});
 }
 
-// i / d for 0 <= i < 2^20, given 1 / d: the half keeps the product 0.5 / d
-// from either neighbouring integer, more than its rounding.
-__device__ __forceinline__ int32_t small_div(int32_t i, float inv) { return int32_t((float(i) + 0.5f) * inv); }
-
 template <bool kDx, typename TX, typename TY, int N, int K, int NBW, int XCAP, int UQ, bool kS1, bool kQuad, bool kEp>
 __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
     typedef PlShape<TX, N, K, NBW, XCAP, UQ, kQuad> S;
@@ -199,7 +196,7 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
 #pragma unroll
         for (int u = 0; u < S::UX; ++u) {
             const int32_t i = S::PER * (lane + 64 * u);  // the tile's pixel
-            const int32_t dr = small_div(rem0 + i, itw), db = small_div(oh0 + dr, iHo);
+            const int32_t dr = row_div(rem0 + i, a.tw, itw), db = row_div(oh0 + dr, a.Ho, iHo);
             const int32_t ih = (oh0 + dr - db * a.Ho) * st - a.ph, iw = (rem0 + i - dr * a.tw) * st - a.pw;
             const bool in = i < S::TP && r0 + dr < a.rows && ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
             xo[u] = in ? int32_t((int64_t(db) * x_img + ih * a.W + iw) * ES) : (kQuad ? 0 : int32_t(kBufferOutOfRange));
@@ -404,8 +401,8 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
         if constexpr (K == 1) {
             xb[nb][0] = unit_of<S::QX>(i);
         } else {
-            const int32_t dr = small_div(rem0 + i, itw), c = rem0 + i - dr * a.tw, rr = min(dr, r1 - r0);
-            const int32_t base = (rr + small_div(oh0 + rr, iHo) * E) * vpitch + c;
+            const int32_t dr = row_div(rem0 + i, a.tw, itw), c = rem0 + i - dr * a.tw, rr = min(dr, r1 - r0);
+            const int32_t base = (rr + row_div(oh0 + rr, a.Ho, iHo) * E) * vpitch + c;
 #pragma unroll
             for (int r = 0; r < K; ++r) xb[nb][r] = unit_of<S::QX>(base + (kS1 ? r : (r % st) * CH + r / st));
         }
@@ -531,7 +528,7 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
     // Pixel of column block nb: image, row and column, or false.
     auto pixel = [&](int nb, int32_t& b, int32_t& oh, int32_t& ow) __attribute__((always_inline)) {
         const int32_t i = rem0 + (wn * NB + nb) * M::COLS + col;
-        const int32_t dr = small_div(i, itw), db = small_div(oh0 + dr, iHo);
+        const int32_t dr = row_div(i, a.tw, itw), db = row_div(oh0 + dr, a.Ho, iHo);
         b = b0 + db;
         oh = oh0 + dr - db * a.Ho;
         ow = strip * a.tw + i - dr * a.tw;
@@ -606,7 +603,7 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
 int32_t pl_strip(int32_t TP, int32_t cap, int32_t items, const PlArgs& a, int32_t K) {
     if (a.W < 4) return 0;                               // a quad lies in one source row
     const int64_t E = (K - 1) / a.s, PL = std::min(a.s, K);
-    for (int32_t k = 1; k <= a.Wo; ++k) {
+    for (int32_t k = std::max(1, a.Wo / cap); k <= a.Wo; ++k) {   // (wider strips than `cap` do not fit)
         const int32_t tw = (a.Wo + k - 1) / k;
         if (k > 1 && tw < 8) break;
         int64_t nr = TP % tw == 0 ? TP / tw : (TP - 2) / tw + 2;

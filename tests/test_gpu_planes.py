@@ -206,3 +206,34 @@ def test_not_finite(k, N, dt, tune):
         _same(dx, rdx)
         if dt == "bf16":
             _same(dD, rdD)
+
+
+def _taps(x, w, k, pd):
+    """conv2d of one stride-1 image as a sum over taps, in fp32 on the GPU (exact on small integers)."""
+    xp = torch.nn.functional.pad(x, (pd, pd, pd, pd))
+    Ho, Wo = xp.shape[2] - k + 1, xp.shape[3] - k + 1
+    y = 0
+    for q in range(k):
+        for r in range(k):
+            y = y + w[:, :, q, r] @ xp[0, :, q:q + Ho, r:r + Wo].reshape(x.shape[1], -1)
+    return y.view(1, -1, Ho, Wo)
+
+
+@pytest.mark.parametrize("m,k,H,W", [
+    (8, 1, 1, 6556022),      # rows and images longer than fp32 reciprocals divide
+    (8, 1, 6556022, 1),
+    (8, 1, 1, 8388628),      # (quads)
+    (8, 1, 2796210, 3),
+    (4, 3, 6556022, 4),
+])
+def test_long_images(m, k, H, W):
+    w, x = workloads.gen_integer_layer(m + k, 16, m, k, 1, H, W)
+    layer = onexn.prepare_layer(w.bfloat16(), 16, 0.0, False)
+    ref = _taps(x.cuda(), w.cuda(), k, k // 2).bfloat16()
+    buf = torch.full((ref.numel() + 4096,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    y = layer.forward(x.bfloat16().cuda(), 1, k // 2, out=buf[:ref.numel()].view(ref.shape))
+    assert torch.equal(y, ref)
+    assert buf[ref.numel():].isnan().all()
+    if k == 1 and H == 1:
+        y = onexn.fc_fwd(layer.P, layer.I, layer.D, 16, x.bfloat16().cuda().view(m, W), "cols")
+        assert torch.equal(y, ref.view(16, W))
