@@ -230,14 +230,20 @@ __global__ void __launch_bounds__(kBfThreads, 3) bwd_data_pw_bf16(BfArgs a) {
     }
 }
 
+constexpr int kBfFewM = 64;          // input channels up to which WM is 2
+
+// Workgroups of a launch (32 wm input channels x 256 / wm pixels each).
+int64_t bf_grid(int wm, int32_t batch, int32_t H, int32_t W, int32_t m) {
+    const int64_t px = 256 / wm, rows = 32 * wm;
+    return (int64_t(batch) * H * W + px - 1) / px * ((m + rows - 1) / rows);
+}
+
 template <int WM, bool kQuad, typename TY>
 onexn_status launch_bf(BfArgs a, hipStream_t s) {
     typedef BfShape<WM> S;
     a.rblocks = (a.m + S::ROWS - 1) / S::ROWS;
-    const int64_t total = (int64_t(a.batch) * a.H * a.W + S::TP - 1) / S::TP * a.rblocks;
-    if (total > INT32_MAX / kBfThreads) return fail(ONEXN_ERR_UNSUPPORTED, "conv2d_bwd_data: grid out of range");
-    a.total = int32_t(total);
-    hipLaunchKernelGGL((bwd_data_pw_bf16<WM, kQuad, TY>), dim3(uint32_t(total)), dim3(kBfThreads), 0, s, a);
+    a.total = int32_t(bf_grid(WM, a.batch, a.H, a.W, a.m));
+    hipLaunchKernelGGL((bwd_data_pw_bf16<WM, kQuad, TY>), dim3(uint32_t(a.total)), dim3(kBfThreads), 0, s, a);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return fail(ONEXN_ERR_HIP, "conv2d_bwd_data: launch failed: %s", hipGetErrorString(err));
     return ONEXN_OK;
@@ -246,7 +252,7 @@ onexn_status launch_bf(BfArgs a, hipStream_t s) {
 }  // namespace
 
 bool bwd_data_pw_bf16_applies(const ConvArgs& a, onexn_dtype wdt, int32_t batch) {
-    (void)batch;
+    if (bf_grid(a.m <= kBfFewM ? 2 : 4, batch, a.H, a.W, a.m) > INT32_MAX / kBfThreads) return false;
     return wdt == ONEXN_BF16 && a.KK == 1 && a.N >= 8 && a.sh == a.sw && a.G <= kBfMaxG &&
            reinterpret_cast<uintptr_t>(a.D) % 16 == 0 && int64_t(a.t) * a.N * 2 < (int64_t(1) << 31);
 }
@@ -276,7 +282,7 @@ onexn_status launch_bwd_data_pw_bf16(const ConvArgs& a, onexn_dtype dxdt, int32_
     const bool quad = a.sh == 1 && a.ph == 0 && a.pw == 0 && a.H * a.W % 4 == 0;
     auto go = [&](auto ty) {
         typedef decltype(ty) TY;
-        if (a.m <= 64) return quad ? launch_bf<2, true, TY>(b, s) : launch_bf<2, false, TY>(b, s);
+        if (a.m <= kBfFewM) return quad ? launch_bf<2, true, TY>(b, s) : launch_bf<2, false, TY>(b, s);
         return quad ? launch_bf<4, true, TY>(b, s) : launch_bf<4, false, TY>(b, s);
     };
     if (dxdt == ONEXN_BF16) return go(uint16_t{});

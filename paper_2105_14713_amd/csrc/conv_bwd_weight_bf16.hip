@@ -305,19 +305,21 @@ __global__ void __launch_bounds__(kDwThreads, 4) bwd_weight_bf16(DwArgs a) {
     }
 }
 
+int64_t dw_tiles(int32_t m, int32_t KK) { return (int64_t(m) * KK + kDwPairs - 1) / kDwPairs; }
+// Most workgroups of a launch (each row block of a col-group takes dw_tiles).
+constexpr int64_t kDwMaxGrid = INT32_MAX / kDwThreads;
+
 template <int N, int R, int MODE>
 onexn_status launch_dw(DwArgs d, hipStream_t s) {
     const int64_t octs = int64_t(d.batch) * d.Ho * d.noct;
     d.chunks = int32_t((octs + kDwOcts - 1) / kDwOcts);
-    d.tiles = int32_t((int64_t(d.m) * d.KK + kDwPairs - 1) / kDwPairs);
+    d.tiles = int32_t(dw_tiles(d.m, d.KK));
     d.dk = kDwOcts % d.noct;
     d.drow = kDwOcts / d.noct;
     d.db = d.drow / d.Ho;
     d.doh = d.drow % d.Ho;
-    const int64_t total = int64_t(d.G) * (N / R) * d.tiles;
-    if (total > INT32_MAX / kDwThreads) return fail(ONEXN_ERR_UNSUPPORTED, "conv2d_bwd_weight: grid out of range");
-    d.total = int32_t(total);
-    hipLaunchKernelGGL((bwd_weight_bf16<N, R, MODE>), dim3(uint32_t(total)), dim3(kDwThreads), 0, s, d);
+    d.total = d.G * (N / R) * d.tiles;
+    hipLaunchKernelGGL((bwd_weight_bf16<N, R, MODE>), dim3(uint32_t(d.total)), dim3(kDwThreads), 0, s, d);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return fail(ONEXN_ERR_HIP, "conv2d_bwd_weight: launch failed: %s", hipGetErrorString(err));
     return ONEXN_OK;
@@ -332,6 +334,7 @@ bool bwd_weight_bf16_applies(const ConvArgs& a, onexn_dtype xdt, int32_t batch) 
     if (batch < 1 || a.t < 1 || xdt != ONEXN_BF16) return false;
     // An octet is read whole inside its tensor.
     if (int64_t(batch) * a.m * a.H * a.W < 8 || int64_t(batch) * a.n * a.HWo < 8) return false;
+    if (a.G * dw_tiles(a.m, a.KK) > kDwMaxGrid) return false;
     // Rows of few columns waste most of their octet.
     if ((dw_flat(a) ? a.HWo : a.Wo) < 4) return false;
     return true;
@@ -376,7 +379,8 @@ onexn_status launch_bwd_weight_bf16(const ConvArgs& a, int32_t batch, const void
         // batch 64 (18) 33 against 41; but 1000 -> 200 at 7x7 (112) 27 against
         // 19 and 256 -> 1024 at 14x14 (144) 65 against 44.
         const int64_t tiles = (int64_t(a.t) * a.KK + kDwPairs - 1) / kDwPairs + a.G / 2;
-        return 8 * tiles < 3 * int64_t(device_cu_count()) ? launch_dw<32, 16, m>(d, s) : launch_dw<32, 32, m>(d, s);
+        const bool half = 8 * tiles < 3 * int64_t(device_cu_count()) && 2 * a.G * dw_tiles(a.m, a.KK) <= kDwMaxGrid;
+        return half ? launch_dw<32, 16, m>(d, s) : launch_dw<32, 32, m>(d, s);
     };
     if (dw_flat(a)) return by_mode(std::integral_constant<int, kFlat>{});
     if (a.sw == 1) return by_mode(std::integral_constant<int, kTap>{});

@@ -618,18 +618,8 @@ int32_t pl_strip(int32_t TP, int32_t cap, int32_t items, const PlArgs& a, int32_
 
 template <bool kDx, typename TX, typename TY, int N, int K, int NBW, int XCAP, int UQ, bool kS1, bool kQuad,
           bool kEp>
-onexn_status launch_plane(PlArgs a, hipStream_t stream) {
-    typedef PlShape<TX, N, K, NBW, XCAP, UQ, kQuad> S;
-    a.tw = K == 1 ? a.Wo : pl_strip(S::TP, S::XP, S::XITEMS, a, K);
-    if (a.tw < 1) return fail(ONEXN_ERR_UNSUPPORTED, "conv2d: the staged tile does not fit");
-    const int64_t strips = (a.Wo + a.tw - 1) / a.tw;
-    a.tps = int32_t((int64_t(a.rows) * a.tw + S::TP - 1) / S::TP);
-    a.rblocks = (a.R + N - 1) / N;
-    const int64_t total = strips * a.tps * a.rblocks;
-    if (total < 1 || total > INT32_MAX / kPlThreads)
-        return fail(ONEXN_ERR_UNSUPPORTED, "conv2d: grid of %lld workgroups is out of range", (long long)total);
-    a.total = int32_t(total);
-    hipLaunchKernelGGL((plane_conv<kDx, TX, TY, N, K, NBW, XCAP, UQ, kS1, kQuad, kEp>), dim3(uint32_t(total)),
+onexn_status launch_plane(const PlArgs& a, hipStream_t stream) {
+    hipLaunchKernelGGL((plane_conv<kDx, TX, TY, N, K, NBW, XCAP, UQ, kS1, kQuad, kEp>), dim3(uint32_t(a.total)),
                        dim3(kPlThreads), 0, stream, a);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return fail(ONEXN_ERR_HIP, "conv2d: launch failed: %s", hipGetErrorString(err));
@@ -644,22 +634,31 @@ constexpr int kPx1 = 256, kCap1 = 528, kPxS = 128, kCapS = 400, kPx2 = 128, kCap
 
 enum PlKind { kPlNone, kPlPoint, kPlPointQuad, kPlS1, kPlS1Small, kPlStrided };
 
-// Workgroups of a kind's tiles (one row block each).
-int64_t pl_tiles(const PlArgs& a, int32_t TP, int32_t tw) {
-    return ((a.Wo + tw - 1) / tw) * ((int64_t(a.rows) * tw + TP - 1) / TP);
+// Sets the launch of tiles of TP pixels in strips of tw columns for blocks of
+// `rows` rows; false if there is no such strip (tw = 0) or the grid is out of range.
+bool pl_grid(PlArgs& a, int32_t TP, int32_t tw, int32_t rows) {
+    if (tw < 1) return false;
+    a.tw = tw;
+    a.tps = int32_t((int64_t(a.rows) * tw + TP - 1) / TP);
+    a.rblocks = (a.R + rows - 1) / rows;
+    const int64_t total = int64_t((a.Wo + tw - 1) / tw) * a.tps * a.rblocks;
+    if (total < 1 || total > INT32_MAX / kPlThreads) return false;
+    a.total = int32_t(total);
+    return true;
 }
 
-PlKind pl_kind(const PlArgs& a, int32_t K, int32_t rows) {
+// Chooses the tile of a layer and sets its launch.
+PlKind pl_choose(PlArgs& a, int32_t K, int32_t rows) {
     if (K == 1) {
         const bool dense = a.s == 1 && a.ph == 0 && a.pw == 0 && int64_t(a.H) * a.W % 4 == 0;
-        return dense ? kPlPointQuad : kPlPoint;
+        return !pl_grid(a, kPx1, a.Wo, rows) ? kPlNone : dense ? kPlPointQuad : kPlPoint;
     }
     if (a.s == 1) {
         const int32_t big = pl_strip(kPx1, kCap1, 128, a, K), small = pl_strip(kPxS, kCapS, 128, a, K);
-        if (big && (!small || pl_tiles(a, kPx1, big) * ((a.R + rows - 1) / rows) > device_cu_count())) return kPlS1;
-        return small ? kPlS1Small : kPlNone;
+        if (pl_grid(a, kPx1, big, rows) && (!small || a.total > device_cu_count())) return kPlS1;
+        return pl_grid(a, kPxS, small, rows) ? kPlS1Small : kPlNone;
     }
-    return pl_strip(kPx2, kCap2, 256, a, K) ? kPlStrided : kPlNone;
+    return pl_grid(a, kPx2, pl_strip(kPx2, kCap2, 256, a, K), rows) ? kPlStrided : kPlNone;
 }
 
 template <bool kDx, typename TX, typename TY, int N, bool kEp>
@@ -678,7 +677,8 @@ onexn_status launch_kind(PlKind kind, const PlArgs& p, hipStream_t s) {
 bool pl_fits(const ConvArgs& a, int32_t batch, int64_t src_img, int es, int64_t dst_px) {
     // A tile of 256 pixels spans at most 257 images.
     if (std::min<int64_t>(batch, 257) * src_img * es >= (int64_t(1) << 31)) return false;
-    if (int64_t(a.t) * a.N * a.KK * es >= (int64_t(1) << 31)) return false;
+    // (Weights past the last block, never read, are addressed up to 64 blocks on.)
+    if ((int64_t(a.t) + 64) * a.N * a.KK * es >= (int64_t(1) << 31)) return false;
     return dst_px < (int64_t(1) << 30);
 }
 
@@ -744,8 +744,8 @@ bool planes_fwd_applies(const ConvArgs& a, onexn_dtype xdt, onexn_dtype ydt, one
     if (!pl_fits(a, batch, a.x_img, es, int64_t(batch) * a.Ho * (a.Wo + 8))) return false;
     if (reinterpret_cast<uintptr_t>(a.D) % (4 * es) != 0) return false;   // quads of weights
     if (xdt == ONEXN_F32 && (ydt != ONEXN_F32 || a.kh != 3 || a.sh != 1)) return false;
-    const PlArgs p = pl_fwd_args(a);
-    const PlKind kind = pl_kind(p, a.kh, a.N);
+    PlArgs p = pl_fwd_args(a);
+    const PlKind kind = pl_choose(p, a.kh, a.N);
     if (kind == kPlNone) return false;
     if (xdt == ONEXN_BF16) return true;
     if (tuning(kTuneKernel) == 2) return true;
@@ -758,11 +758,9 @@ bool planes_fwd_applies(const ConvArgs& a, onexn_dtype xdt, onexn_dtype ydt, one
     // fifth faster by these.  256 -> 256 at 14x14, N = 32, batch 1: 32.5 us
     // against 14.4; batch 64: 60 against 92; 32 -> 32 at 112x112, batch 16:
     // 32.6 against 28.1.
-    const int32_t TP = kind == kPlS1 ? kPx1 : kPxS;
-    const int32_t tw = pl_strip(TP, kind == kPlS1 ? kCap1 : kCapS, 128, p, 3);
-    const double wgs = double(pl_tiles(p, TP, tw)) * a.G, chunks = double(a.t) / a.G / 16 + 0.5;
+    const double wgs = p.total, chunks = double(a.t) / a.G / 16 + 0.5;
     const int64_t cus = device_cu_count();
-    const double px = TP == kPx1 ? 1.0 : 0.7;            // a 128-pixel tile cuts the same weights
+    const double px = kind == kPlS1 ? 1.0 : 0.7;         // a 128-pixel tile cuts the same weights
     const bool n32 = a.N == 32;
     const double each = wgs <= cus ? (n32 ? 3.4 : 3.0) : wgs <= 2.0 * cus ? (n32 ? 6.1 : 5.4) : (n32 ? 7.0 : 5.4);
     const double here = std::max(1.0, wgs / (2.0 * cus)) * ((n32 ? 6.0 : 4.5) + each * px * chunks);
@@ -771,8 +769,8 @@ bool planes_fwd_applies(const ConvArgs& a, onexn_dtype xdt, onexn_dtype ydt, one
 }
 
 onexn_status launch_planes_fwd(const ConvArgs& a, onexn_dtype xdt, onexn_dtype ydt, hipStream_t s) {
-    const PlArgs p = pl_fwd_args(a);
-    const PlKind kind = pl_kind(p, a.kh, a.N);
+    PlArgs p = pl_fwd_args(a);
+    const PlKind kind = pl_choose(p, a.kh, a.N);
     return with_epilogue(a, [&](auto ep) {
         constexpr bool E = decltype(ep)::value;
         auto by_n = [&](auto tx, auto ty) {
@@ -789,13 +787,14 @@ bool planes_dx_applies(const ConvArgs& a, onexn_dtype wdt, int32_t batch) {
     if (a.N < 8 || a.kh != 3 || a.kw != 3 || a.sh != a.sw || (wdt == ONEXN_F32 && a.sh != 1)) return false;
     const int es = wdt == ONEXN_F32 ? 4 : 2;
     if (!pl_fits(a, batch, int64_t(a.n) * a.HWo, es, int64_t(batch) * a.H * (a.W + 8))) return false;
-    return a.G <= kPlMaxRuns && pl_kind(pl_dx_args(a, batch, nullptr, nullptr), 3, 32) != kPlNone;
+    PlArgs p = pl_dx_args(a, batch, nullptr, nullptr);
+    return a.G <= kPlMaxRuns && pl_choose(p, 3, 32) != kPlNone;
 }
 
 onexn_status launch_planes_dx(const ConvArgs& a, onexn_dtype wdt, onexn_dtype dxdt, int32_t batch, const void* dy,
                               void* dx, hipStream_t s) {
-    const PlArgs p = pl_dx_args(a, batch, dy, dx);
-    const PlKind kind = pl_kind(p, 3, 32);
+    PlArgs p = pl_dx_args(a, batch, dy, dx);
+    const PlKind kind = pl_choose(p, 3, 32);
     if (wdt == ONEXN_F32) return launch_kind<true, float, float, 32, false>(kind, p, s);
     if (dxdt == ONEXN_BF16) return launch_kind<true, uint16_t, uint16_t, 32, false>(kind, p, s);
     return launch_kind<true, uint16_t, float, 32, false>(kind, p, s);

@@ -287,3 +287,34 @@ def test_build_mask_dev_checks_arguments_on_the_host(lib):
     assert call(7, 0.5, None) == ERR["ONEXN_ERR_NULL"]
     assert call(7, 0.5, p, 8) == ERR["ONEXN_ERR_BUFSIZE"]
     assert t.value == -1
+
+
+# ---------------------------------------------------------------------------
+# Layers whose grid a specialised kernel cannot launch go to the general one.
+# ---------------------------------------------------------------------------
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="would launch with host pointers on a GPU")
+def test_grid_limits_fall_back(lib):
+    """Without a GPU every accepted call ends in a failed launch (HIP) and every
+    refused one in UNSUPPORTED, so the status tells which sizes are accepted."""
+    buf = torch.zeros(1 << 10)
+    p = buf.data_ptr()
+    bf16 = onexn.BF16
+
+    def fwd(n, m, k, N, t, B, H, W, s):
+        return lib.onexn_conv2d_fwd(p, p, p, bf16, n, m, k, k, N, t, p, bf16, 0, B, H, W, s, s, k // 2, k // 2, p,
+                                    bf16, None)
+
+    def dx(n, m, N, t, B, H, W):
+        return lib.onexn_conv2d_bwd_data(p, p, p, bf16, n, m, 1, 1, N, t, p, bf16, B, H, W, 1, 1, 0, 0, p, bf16, None)
+
+    def dw(n, m, k, N, t, B, H, W):
+        return lib.onexn_conv2d_bwd_weight(p, p, n, m, k, k, N, t, p, bf16, p, B, H, W, 1, 1, k // 2, k // 2, p, None)
+
+    ok = onexn._STATUS_NAMES.index("ONEXN_ERR_HIP")
+    # 39.3 M output pixels x 32 col-groups: 128-pixel strided tiles are too many, 256-pixel ones are not.
+    assert fwd(512, 8, 3, 16, 100, 600, 512, 512, 2) == ok
+    assert dx(1, 1, 8, 1, 1, 32768, 36000) == ok                  # 1.2 G pixels of one channel
+    assert dw(32 * 1100, 65536, 1, 32, 1000, 1, 2, 2) == ok       # 2048 tiles of 1100 col-groups
+    assert dw(32 * 1000, 65536, 1, 32, 1000, 1, 2, 2) == ok       # (half the rows each would be too many)
