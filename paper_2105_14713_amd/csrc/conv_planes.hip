@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
 #pragma unroll
         for (int u = 0; u < S::UX; ++u) {
             const int32_t i = S::PER * (lane + 64 * u);  // the tile's pixel
-            const int32_t dr = row_div(rem0 + i, a.tw, itw), db = row_div(oh0 + dr, a.Ho, iHo);
+            const int32_t dr = small_div(rem0 + i, itw), db = small_div(oh0 + dr, iHo);
             const int32_t ih = (oh0 + dr - db * a.Ho) * st - a.ph, iw = (rem0 + i - dr * a.tw) * st - a.pw;
             const bool in = i < S::TP && r0 + dr < a.rows && ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
             xo[u] = in ? int32_t((int64_t(db) * x_img + ih * a.W + iw) * ES) : (kQuad ? 0 : int32_t(kBufferOutOfRange));
@@ -401,8 +401,8 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
         if constexpr (K == 1) {
             xb[nb][0] = unit_of<S::QX>(i);
         } else {
-            const int32_t dr = row_div(rem0 + i, a.tw, itw), c = rem0 + i - dr * a.tw, rr = min(dr, r1 - r0);
-            const int32_t base = (rr + row_div(oh0 + rr, a.Ho, iHo) * E) * vpitch + c;
+            const int32_t dr = small_div(rem0 + i, itw), c = rem0 + i - dr * a.tw, rr = min(dr, r1 - r0);
+            const int32_t base = (rr + small_div(oh0 + rr, iHo) * E) * vpitch + c;
 #pragma unroll
             for (int r = 0; r < K; ++r) xb[nb][r] = unit_of<S::QX>(base + (kS1 ? r : (r % st) * CH + r / st));
         }
@@ -528,7 +528,7 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
     // Pixel of column block nb: image, row and column, or false.
     auto pixel = [&](int nb, int32_t& b, int32_t& oh, int32_t& ow) __attribute__((always_inline)) {
         const int32_t i = rem0 + (wn * NB + nb) * M::COLS + col;
-        const int32_t dr = row_div(i, a.tw, itw), db = row_div(oh0 + dr, a.Ho, iHo);
+        const int32_t dr = small_div(i, itw), db = small_div(oh0 + dr, iHo);
         b = b0 + db;
         oh = oh0 + dr - db * a.Ho;
         ow = strip * a.tw + i - dr * a.tw;
@@ -649,6 +649,7 @@ bool pl_grid(PlArgs& a, int32_t TP, int32_t tw, int32_t rows) {
 
 // Chooses the tile of a layer and sets its launch.
 PlKind pl_choose(PlArgs& a, int32_t K, int32_t rows) {
+    if (a.Ho > kDivMax || (K == 1 && a.Wo > kDivMax)) return kPlNone;   // divided by (3x3 rows: a strip's width)
     if (K == 1) {
         const bool dense = a.s == 1 && a.ph == 0 && a.pw == 0 && int64_t(a.H) * a.W % 4 == 0;
         return !pl_grid(a, kPx1, a.Wo, rows) ? kPlNone : dense ? kPlPointQuad : kPlPoint;

@@ -9,23 +9,20 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SRC = r"""
-#include <algorithm>
+#include <initializer_list>
 #include "tile_div.h"
 using namespace onexn;
-extern "C" int32_t row(int32_t i, int32_t d) { return row_div(i, d, 1.f / float(d)); }
-extern "C" int32_t small(int32_t i, int32_t d) { return small_div(i, 1.f / float(d)); }
-// The first divisor in [lo, hi), by steps, of which the last and first two
-// offsets of some quotient below `quotients` divide wrongly (0: none).
-extern "C" int32_t first_wrong(int64_t lo, int64_t hi, int64_t step, int64_t quotients, bool use_small, int64_t top) {
-    for (int64_t d = lo; d < hi; d += step) {
+extern "C" int32_t div_max() { return kDivMax; }
+// The first divisor in [lo, hi) for which an offset near a multiple below `top`
+// (and below d + 1024 where `row`) is divided wrongly (0: none).
+extern "C" int32_t first_wrong(int64_t lo, int64_t hi, int64_t top, bool row) {
+    for (int64_t d = lo; d < hi; ++d) {
         const float inv = 1.f / float(int32_t(d));
-        for (int64_t q = 0; q < quotients; ++q)
-            for (int64_t e : {int64_t(0), int64_t(1), d - 1}) {
-                const int64_t i = q * d + e;
-                if (i >= top || e >= d) continue;
-                const int32_t got = use_small ? small_div(int32_t(i), inv) : row_div(int32_t(i), int32_t(d), inv);
-                if (got != i / d) return int32_t(d);
-            }
+        const int64_t end = row ? d + 1024 : top;
+        for (int64_t m = 0; m < end; m += d)
+            for (int64_t i : {m, m + 1, m + d - 1})
+                if (i < end && small_div(int32_t(i), inv) != i / d) return int32_t(d);
+        if (row && small_div(int32_t(d + 1023), inv) != (d + 1023) / d) return int32_t(d);
     }
     return 0;
 }
@@ -41,22 +38,18 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
                     "-I" + os.path.join(ROOT, "paper_2105_14713_amd", "csrc"), src, "-o", so], check=True)
     lib = ctypes.CDLL(so)
-    lib.first_wrong.argtypes = [ctypes.c_int64] * 4 + [ctypes.c_bool, ctypes.c_int64]
+    lib.first_wrong.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_bool]
     return lib
 
 
-def test_row_div_over_image_sizes(lib):
-    """Rows and images of any length (a tile touches up to 257 of them)."""
-    top = 2 ** 31 - 4096
-    assert lib.first_wrong(1, 2 ** 13, 1, 1024, False, top) == 0
-    assert lib.first_wrong(1, 2 ** 24, 1, 3, False, top) == 0
-    assert lib.first_wrong(2 ** 13, 2 ** 24, 509, 258, False, top) == 0
-    assert lib.first_wrong(2 ** 24, top, 4093, 5, False, top) == 0
-    for d in (6556022, 2 ** 22 + 1, 2 ** 30 - 1, 2 ** 30 + 1, top - 1):
-        for i in (d - 1, d, min(d + 255, top - 1)):
-            assert lib.row(i, d) == i // d
+def test_row_offsets(lib):
+    """Rows and images up to the longest that the kernels divide by, and a tile more."""
+    assert lib.first_wrong(1, lib.div_max() + 1, 0, True) == 0
 
 
-def test_small_div_over_tile_counts(lib):
-    assert lib.first_wrong(1, 2 ** 20, 7, 5, True, 2 ** 20) == 0
-    assert lib.first_wrong(1, 4096, 1, 256, True, 2 ** 20) == 0
+def test_the_limit_is_needed(lib):
+    assert lib.first_wrong(1, 1 << 24, 0, True) == 6556022
+
+
+def test_tile_counts(lib):
+    assert lib.first_wrong(1, 4096, 1 << 20, False) == 0
