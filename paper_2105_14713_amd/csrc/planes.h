@@ -1,21 +1,30 @@
 // bf16 operand planes of the matrix-core kernels that run both precisions on
 // the bf16 matrix instructions.
 //
-// A bf16 operand is one plane.  An fp32 operand is three: the value cut (not
-// rounded) to its top 16 bits, the remainder cut likewise, and the rest, which
-// together are the value exactly (3 x 8 significand bits; cutting never
-// overflows).  A product then takes the six plane products of weight 2^-16
-// and above; the three left out are below 2^-24 of it.  a1*b1 goes to one
-// accumulator, the five smaller ones to another, added at the end: the small
-// terms are then not rounded to the large ones' last place.  Measured against
-// 64 bits on normal and ReLU'd operands over contractions of 64 to 50176: 0.4
-// to 0.7 times the error of v_mfma_f32_32x32x2_f32 (one accumulator for all
-// six: 0.85 to 1.5 times, and biased).  Six bf16 products run at 2500 / 6 =
-// 417 TFLOP/s against 157 of the fp32 instruction.
+// A bf16 operand is one plane.  An fp32 operand is three: the value rounded to
+// nearest bf16, the remainder rounded likewise, and the rest.  Each remainder
+// is exact and at most half a unit of the plane above, so the rest fits bf16's
+// 8 significand bits and the planes are the value exactly, down to 2^-110 (below
+// that the rest loses what lies under 2^-133, bf16's last subnormal bit).
+// A product takes the six plane products of weight 2^-16 and above; the three
+// left out, a2*b3 + a3*b2 + a3*b3, are below 2^-24 * (1 + 2^-9) of it (2^-8
+// and 2^-17 bound planes two and three; 0.9 * 2^-24 is the most seen) and
+// have no preferred sign.  (Planes cut instead of rounded leave out up to
+// 2^-21, always towards zero.)  a1*b1 goes to one accumulator, the five
+// smaller ones to another, added at the end: the small terms are then not
+// rounded to the large ones' last place.  Error against 64 bits, as a share of
+// the fp32 instruction's kernels' on normal and ReLU'd operands: forward layers
+// of 512 to 1024 channels that the dispatch takes 0.39 to 0.70, input gradients
+// of 8 to 1024 channels 0.30 to 0.35; single products 1.4 * 2^-24 at most
+// against 1.0 (cut: 7.8), their mean zero.  128 -> 128 3x3 at 28x28, batch 64,
+// N = 32: 63.0 us, 63.7 with planes cut.
+// Six bf16 products run at 2500 / 6 = 417 TFLOP/s against 157 of the fp32
+// instruction.
 //
-// Infinities and NaN do not survive the cut (inf - inf is NaN in the second
-// plane), so a kernel on three planes looks at its accumulators at the end
-// and computes outputs that are not finite again in plain fp32.
+// Infinities, NaN and values that round to infinity do not survive (inf - inf
+// is NaN in the second plane), so a kernel on three planes looks at its
+// accumulators at the end and computes outputs that are not finite again in
+// plain fp32.
 #pragma once
 
 #include "conv_common.h"
@@ -31,35 +40,27 @@ template <typename T> struct Planes;
 template <> struct Planes<float> { static constexpr int NP = 3; typedef float reg; };
 template <> struct Planes<uint16_t> { static constexpr int NP = 1; typedef uint32_t reg; };
 
-// High halves of two words: (lo >> 16) | (hi & 0xffff0000).
-__device__ __forceinline__ uint32_t pack_high(uint32_t lo, uint32_t hi) {
-    return __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+// Two floats rounded to nearest-even bf16, v0 in the low half.
+__device__ __forceinline__ uint32_t round_pair(float v0, float v1) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{v0, v1}), bf16x2));
 }
 
 // Words k of the planes of eight consecutive contraction entries: entries 2k
 // and 2k + 1.
 __device__ __forceinline__ void cut_pair(float v0, float v1, int k, u32x4 (&p)[3]) {
-    uint32_t a = __float_as_uint(v0), b = __float_as_uint(v1);
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
-        p[t][k] = pack_high(a, b);
+        const uint32_t w = round_pair(v0, v1);
+        p[t][k] = w;
         if (t == 2) break;
-        a = __float_as_uint(__uint_as_float(a) - __uint_as_float(a & 0xffff0000u));
-        b = __float_as_uint(__uint_as_float(b) - __uint_as_float(b & 0xffff0000u));
+        v0 -= __uint_as_float(w << 16);
+        v1 -= __uint_as_float(w & 0xffff0000u);
     }
 }
 __device__ __forceinline__ void cut_pair(uint32_t v0, uint32_t v1, int k, u32x4 (&p)[1]) {
     p[0][k] = __builtin_amdgcn_perm(v1, v0, 0x05040100u);
-}
-
-// Eight consecutive contraction entries of one row as planes of 8 bf16.
-__device__ __forceinline__ void to_planes(const float (&v)[8], u32x4 (&p)[3]) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) cut_pair(v[2 * k], v[2 * k + 1], k, p);
-}
-__device__ __forceinline__ void to_planes(const uint32_t (&v)[8], u32x4 (&p)[1]) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) cut_pair(v[2 * k], v[2 * k + 1], k, p);
 }
 
 template <int N> struct PlaneMfma;

@@ -129,11 +129,38 @@ def _norm_err(a, b):
     return np.linalg.norm(a - b) / np.linalg.norm(b)
 
 
+@pytest.mark.parametrize("N", [16, 32])
+def test_fp32_products(N, tune):
+    """One product per output: the planes leave out less than 1.002 * 2^-24 of it,
+    the five small products' additions round by 2^-24 of at most 2^-6 each and
+    the last one by 2^-24: together under 2.1 * 2^-24, with no preferred sign
+    (40000 errors of a spread below 2^-24 average to under 0.05 of it)."""
+    tune("kernel", 2)
+    gen = torch.Generator().manual_seed(N)
+    m, H = 8, 50
+    w = torch.zeros(16, m, 3, 3)
+    o = torch.arange(16)
+    w[o, o % m, 1, 1] = torch.rand(16, generator=gen) + 1
+    x = torch.rand(2, m, H, H, generator=gen) + 1
+    w[1, 1, 1, 1] = x[:, 1, :, :25] = 1 + 2.0 ** -7 - 2.0 ** -23
+    w[2, 2, 1, 1] = x[:, 2, :, :25] = 2 - 2.0 ** -23
+    refs = x.double().numpy()[:, o % m] * w[o, o % m, 1, 1].double().numpy()[:, None, None]
+    y, _ = gpu_conv(w, x, N, 0.0, False, 1, 1)
+    w[m:] = 0                            # (one output channel per input channel)
+    dy = torch.cat([x, x], 1)
+    L = onexn.prepare_layer(w, N, 0.0, False)
+    dx = onexn.conv2d_bwd_data(L.P, L.I, L.D, 16, m, dy.cuda(), (H, H), 1, 1).double().cpu().numpy()
+    for got, ref in ((y, refs), (dx, refs[:, :m])):
+        err = (got / ref - 1) * 2.0 ** 24
+        assert np.abs(err).max() < 2.1
+        assert abs(err.mean()) < 0.05
+
+
 @pytest.mark.parametrize("scale", [1.0, 2.0 ** 60, 2.0 ** -60])
 @pytest.mark.parametrize("N", [16, 32])
 def test_fp32_error(N, scale, tune):
-    """Three planes hold an fp32 value exactly, the six products leave out less
-    than 3 * 2^-24 of a product, and each of at most 9 * 256 / 16 additions per
+    """Three planes hold an fp32 value exactly, the six products leave out at most
+    1.002 * 2^-24 of a product, and each of at most 9 * 256 / 16 additions per
     accumulator rounds by 2^-24 of a partial sum, at random: together under
     sqrt(144) * 2^-24 = 7e-7 of the result's norm, at any scale."""
     tune("kernel", 2)
