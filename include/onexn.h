@@ -286,7 +286,7 @@ onexn_status onexn_fc_fwd(const int32_t* P_dev, const int32_t* I_dev, const void
  * library never reads the environment; until a name is set, and after it is
  * set to -1, the dispatch rules decide.  Names and values:
  *   "kernel"      1: generic gather kernels for every layer; 2: the kernels on
- *                 three bf16 planes for every fp32 layer they can compute
+ *                 bf16 planes for every layer they can compute
  *   "pw_kernel"   1x1 fp32 N = 16/32: 1 resident tile, 3 register operands
  *   "pwb_kernel"  1x1 bf16 N = 32: 1 register-gathered, 2 LDS-staged
  *   "bwd_kernel"  backward: 1 general kernels for every layer, 2 the stride-2

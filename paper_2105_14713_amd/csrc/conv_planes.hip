@@ -735,6 +735,27 @@ PlArgs pl_dx_args(const ConvArgs& a, int32_t batch, const void* dy, void* dx) {
     return p;
 }
 
+// Whether a bf16 1x1 layer is faster here than on the general kernel (64-pixel
+// tiles).  A tile of 256 pixels has little to multiply in a layer of few pixels
+// or a short contraction, and one that spans images of a few pixels loads from
+// as many places as it has images.  us, general and here, p = 0.5, at stride 1:
+//   one-pixel images (samples of an FC layer), 2048 -> 1000, N = 32, batch 1:
+//     74 and 69, 128: 104 and 122, 512: 105 and 176; 256 -> 256, N = 16, 512:
+//     17.5 and 30.2; quads of 2x2 images, 64 -> 64, N = 16, batch 32: 6.6 and 7.1;
+//   not quads, N = 16, 64 -> 64: 7x7, batch 1 6.8 and 8.1, 32 7.5 and 8.0; 57x57,
+//     batch 8 12.1 and 11.2, 128 124 and 88; 128 -> 128, batch 1: 7x7 8.8 and
+//     9.6, 15x15 9.6 and 9.0; 256 -> 256, 5x5, batch 32: 14.9 and 13.7.
+// At stride 2, 28x28: 64 -> 256, N = 16, batch 64: 19.4 and 20.1; 128 -> 128,
+// batch 32: N = 16 11.5 and 10.4, N = 32 11.3 and 11.2; 256 -> 256, N = 32,
+// batch 1 17.1 and 15.7, 32 20.0 and 16.4.
+bool pl_point_preferred(const ConvArgs& a, PlKind kind) {
+    const double kept = double(a.t) / a.G, macs = double(a.npix) * a.t * a.N;
+    if (kind == kPlPointQuad) return a.HWo >= 16 || kept >= 56 || a.npix <= 32;
+    if (a.HWo < 16) return false;
+    if (a.sh == 1) return (kept >= 56 && kept * a.npix >= 6000) || macs >= 5e7;
+    return kept >= 112 || macs >= 2e8;
+}
+
 }  // namespace
 
 bool planes_fwd_applies(const ConvArgs& a, onexn_dtype xdt, onexn_dtype ydt, onexn_layout layout) {
@@ -748,8 +769,8 @@ bool planes_fwd_applies(const ConvArgs& a, onexn_dtype xdt, onexn_dtype ydt, one
     PlArgs p = pl_fwd_args(a);
     const PlKind kind = pl_choose(p, a.kh, a.N);
     if (kind == kPlNone) return false;
-    if (xdt == ONEXN_BF16) return true;
     if (tuning(kTuneKernel) == 2) return true;
+    if (xdt == ONEXN_BF16) return a.kh != 1 || pl_point_preferred(a, kind);
     // fp32: against the fp32 instruction's kernel, which spreads a layer's
     // chunks over all compute units.  Times in us fitted to layers of 64 to
     // 512 channels at batch 1 to 256, at N = 32: a workgroup alone on its

@@ -20,7 +20,7 @@ void clear_error();
 // the dispatch rules.
 enum Tune : int {
     kTuneKernel,       // 1: the generic gather kernels for every layer; 2: the bf16-plane
-                       // kernels for every fp32 layer that they can compute
+                       // kernels for every layer that they can compute
     kTunePwKernel,     // 1x1 fp32 N = 16/32: 1 resident tile, 3 register-operand
     kTunePwWgs,        // resident-tile 1x1: workgroups
     kTunePwbGp,        // register-gathered bf16: pixels per granule (4, 8)

@@ -52,6 +52,23 @@ def test_forward_integers(n, m, k, s, pd, B, H, W, N, dt, tune):
         np.testing.assert_array_equal(y, ref)
 
 
+@pytest.mark.parametrize("m,s,B,H,W", [
+    (40, 1, 70, 1, 1),       # one-pixel images
+    (300, 1, 70, 1, 1),
+    (40, 1, 3, 2, 2), (40, 1, 40, 2, 2), (140, 1, 40, 2, 2),     # quads, below and above 32 pixels
+    (40, 1, 2, 7, 7), (140, 1, 1, 7, 7), (140, 1, 2, 7, 7),
+    (40, 2, 3, 9, 9), (230, 2, 3, 9, 9), (230, 2, 9, 5, 5),
+    (40, 1, 1, 211, 211), (70, 2, 8, 211, 211),                  # few channels, many pixels
+])
+@pytest.mark.parametrize("N", [16, 32])
+def test_bf16_1x1_dispatch(m, s, B, H, W, N):
+    """1x1 layers on either side of the lines between the general and this kernel."""
+    w, x = workloads.gen_integer_layer(m + B, 40, m, 1, B, H, W)
+    y, _ = gpu_conv(w.bfloat16(), x.bfloat16(), N, 0.5, True, s, 0, out_dtype=torch.float32)
+    ref, _ = oracle_conv(w, x, N, 0.5, True, s, 0)
+    np.testing.assert_array_equal(y, ref)
+
+
 BWD = [  # (n, m, k, stride, pad, B, H, W, N)
     (40, 33, 3, 1, 1, 2, 16, 16, 32),
     (64, 50, 3, 1, 1, 3, 14, 14, 16),
