@@ -410,7 +410,8 @@ extern "C" onexn_status onexn_conv2d_bwd_data(const int32_t* P_dev, const int32_
         if (bwd_data_fewc_applies(a, wdt, dxdt, batch)) return launch_bwd_data_fewc(a, batch, dy_dev, dx_dev, s);
         if (bwd_data_pw_bf16_applies(a, wdt, batch))
             return launch_bwd_data_pw_bf16(a, dxdt, batch, dy_dev, dx_dev, s);
-        if (tuning(kTuneBwdKernel) < 0 && planes_dx_applies(a, wdt, batch)) return launch_planes_dx(a, wdt, dxdt, batch, dy_dev, dx_dev, s);
+        if ((tuning(kTuneBwdKernel) < 0 || tuning(kTuneBwdKernel) == 4) && planes_dx_applies(a, wdt, batch))
+            return launch_planes_dx(a, wdt, dxdt, batch, dy_dev, dx_dev, s);
         if (bwd_data_pw_applies(a, wdt, dxdt, batch)) return launch_bwd_data_pw(a, dy_dev, dx_dev, s);
     }
     if (wdt == ONEXN_F32) return launch_bwd_data<float, float>(a, batch, dy_dev, dx_dev, s);

@@ -327,6 +327,28 @@ onexn_status launch_dw(DwArgs d, hipStream_t s) {
 
 bool dw_flat(const ConvArgs& a) { return a.KK == 1 && a.sh == 1 && a.sw == 1 && a.ph == 0 && a.pw == 0; }
 
+// Whether a layer with strided columns, whose octets are loaded element by
+// element, is faster here than on the general kernel.  us fitted to both over
+// 690 layers: 0.07 per octet here, a fifth more of it per column that a short
+// row lacks; there 0.009 per pixel at N = 16 and 0.0175 at N = 32, and more
+// with the (block, tap) pairs, one workgroup each.  General and here, at stride
+// 2: 64 -> 64 1x1 at 7x7, batch 64: N = 16 12.0 and 33.2, N = 32 20.0 and 33.2;
+// at 28x28, batch 64: N = 16 158 and 133, N = 32 438 and 133; 256 -> 256 1x1 at
+// 7x7, batch 8, N = 16: 13.0 and 7.7; 64 -> 64 3x3 at 9x9, batch 64, N = 16:
+// 23.8 and 33.2.  The worst choice of the fit: 256 -> 64 3x3 at 7x7, batch 64, N
+// = 16, taken here at 54 against 42.
+bool dw_strided_preferred(const ConvArgs& a, int32_t batch) {
+    const double px = double(batch) * a.HWo, pairs = double(a.t) * a.KK, octs = double(batch) * a.Ho * ((a.Wo + 7) / 8);
+    const bool n16 = a.N == 16;
+    const double here = 2.8 + 0.0725 * octs * (1 + 0.15 * std::max(0, 8 - a.Wo));
+    const double per_px = std::max(n16 ? 0.009 : 0.0175, pairs * (n16 ? 0.8e-5 : 1.7e-5));
+    // (It reads its operands once per pair: slower when an L2 does not hold them.)
+    const double mb = 2e-6 * batch * (double(a.m) * a.H * a.W + double(a.n) * a.HWo);
+    const double far = 1 + std::min(1.0, std::max(0.0, mb - 3) / 4);
+    const double general = 4.5 + pairs * (n16 ? 0.002 : 0.005) + px * far * (a.Wo < 5 ? 0.8 : 1.0) * per_px;
+    return here < general;
+}
+
 }  // namespace
 
 bool bwd_weight_bf16_applies(const ConvArgs& a, onexn_dtype xdt, int32_t batch) {
@@ -337,7 +359,7 @@ bool bwd_weight_bf16_applies(const ConvArgs& a, onexn_dtype xdt, int32_t batch) 
     if (a.G * dw_tiles(a.m, a.KK) > kDwMaxGrid) return false;
     // Rows of few columns waste most of their octet.
     if ((dw_flat(a) ? a.HWo : a.Wo) < 4) return false;
-    return true;
+    return a.sw == 1 || tuning(kTuneBwdKernel) == 4 || dw_strided_preferred(a, batch);
 }
 
 onexn_status launch_bwd_weight_bf16(const ConvArgs& a, int32_t batch, const void* x, const void* dy, float* dD,

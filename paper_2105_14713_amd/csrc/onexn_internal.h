@@ -36,7 +36,8 @@ enum Tune : int {
     kTunePwbWgs,       // LDS-staged bf16 1x1: workgroups
     kTuneKxfSplit,     // 3x3 FMA (N <= 8): waves per unit (1, 4)
     kTuneNhwcTile,     // NHWC 1x1: column blocks per tile
-    kTuneBwdKernel,    // backward: 1 the general kernels for every layer
+    kTuneBwdKernel,    // backward: 1 the general kernels for every layer, 4 the bf16 weight
+                       // gradient's matrix-core kernel for every layer that it can compute
     kTuneBwdSplit,     // 1x1 weight gradient: pixel ranges per tile
     kTuneCount
 };

@@ -103,11 +103,13 @@ def _grads(w, x, dy, N, p, s, pd):
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("n,m,k,s,pd,B,H,W,N", BWD)
-def test_gradients_integers(n, m, k, s, pd, B, H, W, N, dt):
+def test_gradients_integers(n, m, k, s, pd, B, H, W, N, dt, tune):
     w, x = workloads.gen_integer_layer(n + m + W, n, m, k, B, H, W)
     Ho, Wo = onexn.out_hw(H, W, k, k, (s, s), (pd, pd))
     dy = torch.randint(-3, 4, (B, n, Ho, Wo), generator=torch.Generator().manual_seed(W)).float()
-    for p in (0.0, 0.5, 0.95):
+    strided = dt == "bf16" and s > 1     # the general kernel may be chosen there, by times
+    for kernel, p in [(4, 0.0), (4, 0.5), (4, 0.95)] + [(-1, 0.5)] * strided:
+        tune("bwd_kernel", kernel if strided else -1)
         L, dx, dD = _grads(w.to(DTYPES[dt]), x.to(DTYPES[dt]), dy.to(DTYPES[dt]), N, p, s, pd)
         pr = oracle.prune(w.double().numpy(), N, p, True)
         np.testing.assert_array_equal(
@@ -129,7 +131,8 @@ def test_bf16_weight_gradient_does_not_vary():
     (170, 1400, 32),   # a 1x1 layer of many tiles: all 32 rows; 10 rows in the last col-group
     (170, 30, 16),
 ])
-def test_bf16_weight_gradient_rows(n, m, N, k, s, pd):
+def test_bf16_weight_gradient_rows(n, m, N, k, s, pd, tune):
+    tune("bwd_kernel", 4)
     if k == 3:
         m = max(m // 9, 30)
     w, x = workloads.gen_integer_layer(n + m, n, m, k, 2, 10, 8)
