@@ -24,11 +24,14 @@
 // pixels, and a layer has t * KK / 32 workgroups of pairs.  256 -> 1024 at
 // 14x14, batch 64, N = 32 (t = 4096): 1920 us with one workgroup per block and
 // lanes along the pixels, without matrix cores; 44 us here.  64 -> 256 at 56x56
-// (16 tiles of pairs for 256 compute units): 6722 and 495 us.
+// (16 tiles of pairs for 256 compute units): 7090 and 410 us.
 //
 // Sums that are not finite are computed again in plain fp32 over the pixels
 // whose tap lies inside the image (masked columns multiply as zeros, and zero
-// times infinity is NaN).
+// times infinity is NaN), a wave per sum,
+// until it is NaN.  256 -> 1024 1x1 at 14x14, batch 64 (44 us): 52 us with a NaN
+// in dY, 163 with an infinity, 250 with nothing else in it; 64 -> 256 at 56x56
+// (410 us): 410, 2300 and 500 (by one thread per sum: 33, 32 and 48 ms).
 
 #include <algorithm>
 #include <utility>
@@ -264,44 +267,66 @@ __global__ void __launch_bounds__(kDwThreads, 4) bwd_weight_bf16(DwArgs a) {
     }
 
     // ---- Sums over the waves of a pair block, in wave order, and the store:
-    // entry (row, pair) at dD[z][row][tap].
-    auto finish = [&](int32_t row, int32_t pr, float v) __attribute__((always_inline)) {
-        if (pr >= pairs) return;
-        const int32_t tap = pr / cnt, z = zb + pr - tap * cnt;
-        if (not_finite(v)) {
-            // Plain fp32 over the pixels inside the image.
-            const int32_t c = a.I[z], q = tap / a.kw, r = tap - q * a.kw;
-            v = 0.f;
-            if (c >= 0 && c < a.m && g * N + row < a.n) {
-                for (int32_t p = 0; p < a.chunks * kDwOcts; ++p) {
-                    const int32_t orow = p / a.noct, bb = orow / a.Ho, oo = orow - bb * a.Ho;
-                    if (bb >= a.batch) break;
-                    const int32_t ih = oo * a.sh - a.ph + q, w0 = 8 * (p - orow * a.noct);
-                    if (ih < 0 || ih >= a.H) continue;
-                    for (int32_t ow = w0; ow < min(w0 + 8, a.Wo); ++ow) {
-                        const int32_t iw = ow * a.sw - a.pw + r;
-                        if (iw < 0 || iw >= a.W) continue;
-                        v = fmaf(to_f32(dy[(int64_t(bb) * a.n + g * N + row) * HWo + oo * a.Wo + ow]),
-                                 to_f32(x[(int64_t(bb) * a.m + c) * HW + ih * a.W + iw]), v);
-                    }
-                }
-            }
-        }
-        a.dD[(int64_t(z) * N + row) * a.KK + tap] = g * N + row < a.n ? v : 0.f;
-    };
+    // entry (row, pair) at dD[z][row][tap].  A thread sums one entry at most.
     float* const part = reinterpret_cast<float*>(sU);
     constexpr int E = NB * M::ACC * 64;                  // entries of a wave's tile
+    static_assert(E <= kDwThreads, "one entry per thread");
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int r = 0; r < M::ACC; ++r) part[wave * E + (nb * M::ACC + r) * 64 + lane] = acc[nb].value(r);
     __syncthreads();
-    for (int e = tid; e < E; e += kDwThreads) {
-        const int l = e & 63, nr = e >> 6;
+    auto entry_row = [&](int e) { return r0 + M::row(e & 63, (e >> 6) % M::ACC); };
+    auto entry_pair = [&](int e) { return pr0 + ((e >> 6) / M::ACC) * M::COLS + (e & 63) % M::COLS; };
+    auto put = [&](int32_t row, int32_t pr, float v) __attribute__((always_inline)) {
+        const int32_t tap = pr / cnt, z = zb + pr - tap * cnt;
+        a.dD[(int64_t(z) * N + row) * a.KK + tap] = v;
+    };
+    bool bad = false;                                    // to be computed again
+    if (tid < E) {
         float v = 0.f;
 #pragma unroll
-        for (int j = 0; j < kDwWaves; ++j) v += part[j * E + e];
-        finish(r0 + M::row(l, nr % M::ACC), pr0 + (nr / M::ACC) * M::COLS + l % M::COLS, v);
+        for (int j = 0; j < kDwWaves; ++j) v += part[j * E + tid];
+        const int32_t row = entry_row(tid), pr = entry_pair(tid);
+        const bool real = g * N + row < a.n;
+        bad = pr < pairs && real && not_finite(v);
+        if (pr < pairs && !bad) put(row, pr, real ? v : 0.f);
+    }
+    if (!__syncthreads_or(bad)) return;
+
+    // Again in plain fp32 over the pixels inside the image: a wave per entry, a
+    // lane per octet, and the lanes' sums in a fixed order.  A sum that is NaN
+    // stays NaN.
+    int32_t* const list = reinterpret_cast<int32_t*>(sU);
+    if (tid == 0) list[0] = 0;
+    __syncthreads();
+    if (bad) list[1 + atomicAdd(&list[0], 1)] = tid;
+    __syncthreads();
+    const int32_t left = list[0], rows = a.batch * a.Ho;
+#pragma unroll 1
+    for (int32_t i = wave; i < left; i += kDwWaves) {
+        const int e = list[1 + i];
+        const int32_t row = entry_row(e), pr = entry_pair(e);
+        const int32_t tap = pr / cnt, c = a.I[zb + pr - tap * cnt], q = tap / a.kw, r = tap - q * a.kw;
+        float v = 0.f;
+        if (c >= 0 && c < a.m) {
+#pragma unroll 1
+            for (int32_t p0 = 0; p0 < a.chunks * kDwOcts && !__any(v != v); p0 += 64) {
+                const int32_t p = p0 + lane, orow = p / a.noct, bb = orow / a.Ho, oo = orow - bb * a.Ho;
+                const int32_t ih = oo * a.sh - a.ph + q, w0 = 8 * (p - orow * a.noct);
+                if (orow >= rows || ih < 0 || ih >= a.H) continue;
+                const uint16_t* const yr = dy + (int64_t(bb) * a.n + g * N + row) * HWo + oo * a.Wo;
+                const uint16_t* const xr = x + (int64_t(bb) * a.m + c) * HW + ih * a.W;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int32_t ow = w0 + j, iw = ow * a.sw - a.pw + r;
+                    if (ow < a.Wo && iw >= 0 && iw < a.W) v = fmaf(to_f32(yr[ow]), to_f32(xr[iw]), v);
+                }
+            }
+        }
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) v += __shfl_xor(v, d);
+        if (lane == 0) put(row, pr, v);
     }
 }
 

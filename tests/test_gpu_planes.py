@@ -255,6 +255,25 @@ def test_not_finite(k, N, dt, tune):
             _same(dD, rdD)
 
 
+@pytest.mark.parametrize("k,s,N", [(3, 1, 32), (1, 1, 16), (3, 2, 16), (1, 2, 32)])
+def test_not_finite_many_pixels(k, s, N, tune):
+    """Recomputed sums of several passes of a wave's lanes, whole rows of them, and
+    infinities that meet their opposite or a zero late."""
+    tune("bwd_kernel", 4)
+    w, x = workloads.gen_integer_layer(k + N, N + 9, 48, k, 5, 23, 21)
+    Ho, Wo = onexn.out_hw(23, 21, k, k, (s, s), (k // 2, k // 2))
+    dy = torch.randint(1, 4, (5, N + 9, Ho, Wo), generator=torch.Generator().manual_seed(N)).float()
+    inf = float("inf")
+    x[:, 5], x[4, 6, 22, 20], x[0, 7, 0, 0], x[4, 7, 11, 11], x[2, 8] = inf, -inf, inf, -inf, float("nan")
+    dy[0, 3], dy[4, 4, Ho - 1, Wo - 1], dy[2, N + 2, 4, 4] = -inf, inf, float("nan")
+    w, x, dy = (v.bfloat16() for v in (w, x, dy))
+    with np.errstate(invalid="ignore"):
+        L, dx, dD = _grads(w, x, dy, N, 0.3, s, k // 2)
+        rdx, rdD = _kept_grads(L, x.double().numpy(), dy.double().numpy(), k, s, k // 2)
+        _same(dx, rdx)
+        _same(dD, rdD)
+
+
 def _taps(x, w, k, pd):
     """conv2d of one stride-1 image as a sum over taps, in fp32 on the GPU (exact on small integers)."""
     xp = torch.nn.functional.pad(x, (pd, pd, pd, pd))
