@@ -48,8 +48,13 @@
 // batch 64: 3474 us against 56).
 //
 // Non-finite results.  Planes of infinities are NaN, and the dense gradient
-// multiplies pruned zeros; a wave that ends with an accumulator that is not
-// finite computes its outputs again in plain fp32 over the kept blocks only.
+// multiplies pruned zeros; outputs that are not finite are computed again in
+// plain fp32 over the kept blocks only, four rows of a lane's pixel at a time.
+// us with a NaN or an infinity in the source, and with nothing else in it: fp32
+// 128 -> 128 3x3 at 28x28, batch 64: 74, 412 and 99 (73 finite; one output at a
+// time 4050, 4030 and 8800), its input gradient 620, 630 and 1220 (118; 7700 and
+// 17400); bf16 input gradient of 256 -> 256 at 14x14: 2140, 2180 and 1400 (57;
+// 16400 and 17700).
 
 #include <algorithm>
 #include <utility>
@@ -534,65 +539,114 @@ __global__ void __launch_bounds__(kPlThreads, 2) plane_conv(PlArgs a) {
         ow = strip * a.tw + i - dr * a.tw;
         return r0 + dr < a.rows && ow < a.Wo;
     };
-    if (kCheck && bad) {
-        // Plain fp32 over the kept blocks (see the top of the file).
-        const TX* const D = static_cast<const TX*>(a.D);
-#pragma unroll 1
-        for (int nb = 0; nb < NB; ++nb) {
-            int32_t b, oh, ow;
-            if (!pixel(nb, b, oh, ow)) continue;
-            const TX* const x = static_cast<const TX*>(a.x) + int64_t(b) * x_img;
-            TY* const yp = static_cast<TY*>(a.y) + int64_t(b) * a.R * HWo + oh * a.Wo + ow;
-            const int32_t hb = oh * st - a.ph, wb = ow * st - a.pw;
-#pragma unroll 1
-            for (int r = 0; r < M::ACC; ++r) {
-                const int rr = M::row(lane, r);
-                const int32_t o = c0 + rr;      // destination channel
-                if (o >= a.R) continue;
-                float v = 0.f;
-                auto taps = [&](int32_t c, int64_t w0) {
-#pragma unroll 1
-                    for (int tap = 0; tap < KK; ++tap) {
-                        const int32_t vh = hb + tap / K, vw = wb + tap % K, dil = kDx ? a.dil : 1;
-                        const int32_t ih = vh / dil, iw = vw / dil;
-                        const bool in = vh >= 0 && ih < a.H && vw >= 0 && iw < a.W && ih * dil == vh && iw * dil == vw;
-                        if (kDx && !in) continue;
-                        const float xf = in ? to_f32(x[int64_t(c) * a.H * a.W + int64_t(ih) * a.W + iw]) : 0.f;
-                        v = fmaf(xf, to_f32(D[w0 + (kDx ? KK - 1 - tap : tap)]), v);
-                    }
-                };
-                if constexpr (kDx) {
-#pragma unroll 1
-                    for (int32_t g = 0; g < a.G; ++g) {
-                        const uint32_t mask = sMask[g];
-                        if (!((mask >> rr) & 1)) continue;
-                        const int64_t z = sFirst[g] + __popc(mask & ((1u << rr) - 1));
-                        const int32_t lim = min(a.NG, a.C - g * a.NG);
-#pragma unroll 1
-                        for (int32_t i = 0; i < lim; ++i) taps(g * a.NG + i, (z * a.NG + i) * KK);
-                    }
-                } else {
-#pragma unroll 1
-                    for (int32_t z = zb; z < ze; ++z) {
-                        const int32_t c = a.I[z];
-                        if (c >= 0 && c < a.C) taps(c, (int64_t(z) * N + rr) * KK);
-                    }
-                }
-                put(yp + int64_t(o) * HWo, rr, v);
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
+    // Stores column block nb but for the rows in `skip`.
+    auto store_block = [&](int nb, uint32_t skip) __attribute__((always_inline)) {
         int32_t b, oh, ow;
-        if (!pixel(nb, b, oh, ow)) continue;
+        if (!pixel(nb, b, oh, ow)) return;
         TY* const yp = static_cast<TY*>(a.y) + int64_t(b) * a.R * HWo + oh * a.Wo + ow;
 #pragma unroll
         for (int r = 0; r < M::ACC; ++r) {
             const int rr = M::row(lane, r);
             const int32_t o = c0 + rr;
-            if (o < a.R) put(yp + int64_t(o) * HWo, rr, acc[nb].value(r));
+            if (o < a.R && !((skip >> r) & 1)) put(yp + int64_t(o) * HWo, rr, acc[nb].value(r));
+        }
+    };
+    if (!bad) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) store_block(nb, 0);
+        return;
+    }
+    if constexpr (kCheck) {
+        // Outputs that are not finite: plain fp32 over the kept blocks (see the
+        // top of the file), four rows of a column block together (more cost the
+        // kernel registers), until all of them are NaN, which they then stay.
+        uint32_t again[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            int32_t b, oh, ow;
+            again[nb] = 0;
+#pragma unroll
+            for (int r = 0; r < M::ACC; ++r)
+                again[nb] |= uint32_t(not_finite(acc[nb].value(r)) && c0 + M::row(lane, r) < a.R) << r;
+            if (!pixel(nb, b, oh, ow)) again[nb] = 0;
+            store_block(nb, again[nb]);
+        }
+        const TX* const D = static_cast<const TX*>(a.D);
+#pragma unroll 1
+        for (int four = 0; four < NB * M::ACC / 4; ++four) {
+            const int nb = four / (M::ACC / 4), q4 = 4 * (four - nb * (M::ACC / 4));
+            uint32_t rows = again[0];
+#pragma unroll
+            for (int i = 1; i < NB; ++i) rows = nb == i ? again[i] : rows;
+            rows = (rows >> q4) & 15;
+            if (!__any(rows != 0)) continue;
+            int32_t b, oh, ow;
+            pixel(nb, b, oh, ow);
+            const TX* const x = static_cast<const TX*>(a.x) + int64_t(b) * x_img;
+            const int32_t hb = oh * st - a.ph, wb = ow * st - a.pw, dil = kDx ? a.dil : 1;
+            const int row0 = M::row(lane, q4);           // the four are consecutive
+            float v[4] = {0.f, 0.f, 0.f, 0.f};
+            auto open = [&]() __attribute__((always_inline)) {
+                bool o = false;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o |= ((rows >> r) & 1) && v[r] == v[r];
+                return __any(o);
+            };
+            int32_t at[KK];                              // source pixel under each tap, or -1
+#pragma unroll
+            for (int tap = 0; tap < KK; ++tap) {
+                const int32_t vh = hb + tap / K, vw = wb + tap % K, ih = vh / dil, iw = vw / dil;
+                const bool in = vh >= 0 && ih < a.H && vw >= 0 && iw < a.W && ih * dil == vh && iw * dil == vw;
+                at[tap] = rows && in ? ih * a.W + iw : -1;
+            }
+            auto load = [&](int32_t c, float (&xf)[KK]) __attribute__((always_inline)) {
+                const TX* const xc = x + int64_t(c) * a.H * a.W;
+#pragma unroll
+                for (int tap = 0; tap < KK; ++tap) xf[tap] = at[tap] >= 0 ? to_f32(xc[at[tap]]) : 0.f;
+            };
+            float xf[KK];
+            if constexpr (kDx) {
+#pragma unroll 1
+                for (int32_t g = 0; g < a.G && open(); ++g) {
+                    const uint32_t mask = sMask[g];
+                    if (!mask) continue;
+                    const TX* w[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        w[r] = D + int64_t(sFirst[g] + __popc(mask & ((1u << (row0 + r)) - 1))) * a.NG * KK;
+                    const uint32_t kept = mask >> row0;
+                    const int32_t lim = min(a.NG, a.C - g * a.NG);
+#pragma unroll 1
+                    for (int32_t i = 0; i < lim; ++i) {
+                        load(g * a.NG + i, xf);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            if (!((kept >> r) & 1)) continue;
+#pragma unroll
+                            for (int tap = 0; tap < KK; ++tap) {
+                                const float p = fmaf(xf[tap], to_f32(w[r][i * KK + KK - 1 - tap]), v[r]);
+                                v[r] = at[tap] >= 0 ? p : v[r];
+                            }
+                        }
+                    }
+                }
+            } else {
+#pragma unroll 1
+                for (int32_t z = zb; z < ze && open(); ++z) {
+                    const int32_t c = a.I[z];
+                    if (c < 0 || c >= a.C) continue;
+                    load(c, xf);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int tap = 0; tap < KK; ++tap)
+                            v[r] = fmaf(xf[tap], to_f32(D[(int64_t(z) * N + row0 + r) * KK + tap]), v[r]);
+                }
+            }
+            TY* const yp = static_cast<TY*>(a.y) + int64_t(b) * a.R * HWo + oh * a.Wo + ow;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if ((rows >> r) & 1) put(yp + int64_t(c0 + row0 + r) * HWo, row0 + r, v[r]);
         }
     }
 }
