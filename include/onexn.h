@@ -92,8 +92,10 @@ onexn_status onexn_build_mask(const void* w, onexn_dtype wdt, int32_t n, int32_t
  *           the caller; nothing in it needs initialising, and it must not be
  *           reused until the work enqueued here has finished.
  * stream:   hipStream_t (NULL = the null stream).  Enqueues its kernels (up
- *           to seven) and returns without waiting; mask_dev holds
- *           intermediate counts until the last one has run.
+ *           to seven) and returns without waiting.  A mask_dev in device
+ *           memory holds intermediate counts until the last one has run;
+ *           elsewhere (mapped host memory) each byte is written once, and one
+ *           workgroup selects (slower from 16384 blocks on).
  * Errors:   NULL, DTYPE, ARG (sizes, N < 1, p outside [0, 1], misaligned
  *           workspace), BUFSIZE (too small a workspace, layer beyond int32
  *           indexing), HIP (launch failed).  On an error nothing is enqueued

@@ -39,7 +39,9 @@
 //                      does).  The counts and the list live in the mask's own
 //                      bytes until mask_write overwrites them, and the pivot
 //                      in the workspace where the norms were, so the
-//                      workspace is no larger for it.
+//                      workspace is no larger for it.  (A mask outside device
+//                      memory, which need not take atomics, is written once:
+//                      mask_pivot then selects over all scores.)
 //
 // 2048 -> 2048 at N = 32, fp32, rearranged (131072 blocks, 16.8 MB of
 // weights): 708 us with one wave per filter, a rank loop over eight
@@ -536,8 +538,8 @@ __global__ void __launch_bounds__(kSelThreads) mask_pivot(const double* __restri
     __shared__ int32_t sIdx[Sel::kCand];
     __shared__ int64_t sLeft;
     const int tid = threadIdx.x;
-    const uint32_t count = sel->count;
-    if (count > uint32_t(Sel::kCand)) {
+    const uint32_t count = sel ? sel->count : 0;
+    if (!sel || count > uint32_t(Sel::kCand)) {
         const Pivot p = select_all(K, kept, [&](int64_t i) { return order_key(score[i]); });
         if (tid == 0) *pivot = p;
         return;
@@ -611,6 +613,13 @@ void launch_multi(const TW* w, const int32_t* perm, int32_t n, int32_t m, int32_
     hipLaunchKernelGGL(mask_write, kgrid, dim3(256), 0, s, score, K, pivot, mask);
 }
 
+bool in_device_memory(const void* p) {
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) == hipSuccess) return at.type == hipMemoryTypeDevice;
+    (void)hipGetLastError();                       // memory that the runtime does not know
+    return false;
+}
+
 template <typename TW>
 onexn_status launch_mask(const TW* w, int32_t n, int32_t m, int32_t kh, int32_t kw, int32_t N,
                          int64_t kept, int32_t rearrange, int32_t* perm, uint8_t* mask, void* ws,
@@ -624,7 +633,8 @@ onexn_status launch_mask(const TW* w, int32_t n, int32_t m, int32_t kh, int32_t 
     // scratch fits the mask: about even there (512 x 1024 at N = 32, 16384
     // blocks, rearranged: 37 us; 16368 blocks in one workgroup: 38 us), and the
     // one workgroup's time grows with the blocks.
-    const bool all = kept <= 0 || kept >= K, multi = !all && K >= kSmallMin;
+    const bool all = kept <= 0 || kept >= K, large_layer = !all && K >= kSmallMin;
+    const bool multi = large_layer && in_device_memory(mask);
     uint8_t* const aligned = reinterpret_cast<uint8_t*>((reinterpret_cast<uintptr_t>(mask) + 7) & ~uintptr_t(7));
     SelSmall* const small = reinterpret_cast<SelSmall*>(aligned);
     SelLarge* const large = reinterpret_cast<SelLarge*>(aligned);
@@ -641,7 +651,11 @@ onexn_status launch_mask(const TW* w, int32_t n, int32_t m, int32_t kh, int32_t 
     } else if (!multi) {
         hipLaunchKernelGGL((mask_block_scores<TW, 0>), kgrid, dim3(256), 0, s, w, perm, n, m, kh * kw, N, G, score,
                            static_cast<uint32_t*>(nullptr));
-        if (K <= kFewKeys)
+        if (large_layer) {
+            hipLaunchKernelGGL(mask_pivot<SelLarge>, dim3(1), dim3(kSelThreads), 0, s, score, K, kept,
+                               static_cast<const SelLarge*>(nullptr), pivot);
+            hipLaunchKernelGGL(mask_write, kgrid, dim3(256), 0, s, score, K, pivot, mask);
+        } else if (K <= kFewKeys)
             hipLaunchKernelGGL(mask_select<kFewKeys>, dim3(1), dim3(kSelThreads), 0, s, score, int32_t(K), kept, mask);
         else
             hipLaunchKernelGGL(mask_select<kLdsKeys>, dim3(1), dim3(kSelThreads), 0, s, score, int32_t(K), kept, mask);

@@ -144,3 +144,22 @@ def test_selection_sizes(blocks, kind):
         ref = torch.zeros(blocks, dtype=torch.uint8)
         ref[torch.sort(key, descending=True, stable=True).indices[:t]] = 1
         assert torch.equal(mask.reshape(-1), ref)
+
+
+@pytest.mark.parametrize("shape,N", [((64, 64), 8), ((512, 512), 8), ((512, 1024), 8)])
+def test_mask_in_host_memory(shape, N):
+    """A mask in mapped host memory, which device atomics need not reach, is
+    written byte by byte (512, 32768 and 65536 blocks)."""
+    lib = onexn.load_library()
+    w = torch.randn(*shape, 1, 1, generator=torch.Generator().manual_seed(N))
+    n, m = shape
+    wd, perm = w.cuda(), torch.empty(n, dtype=torch.int32, device="cuda")
+    mask = torch.full((m, n // N), 7, dtype=torch.uint8, pin_memory=True)
+    ws = torch.empty(onexn.mask_workspace_bytes(n, m, N), dtype=torch.uint8, device="cuda")
+    t = ctypes.c_int64(-1)
+    st = lib.onexn_build_mask_dev(wd.data_ptr(), 0, n, m, 1, 1, N, 0.5, 1, perm.data_ptr(), mask.data_ptr(),
+                                  ctypes.addressof(t), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    torch.cuda.synchronize()
+    perm_h, mask_h, t_h = onexn.build_mask(w, N, 0.5, True)
+    assert t.value == t_h and torch.equal(perm.cpu(), perm_h) and torch.equal(mask, mask_h)
