@@ -118,6 +118,39 @@ def test_gradients_integers(n, m, k, s, pd, B, H, W, N, dt, tune):
         np.testing.assert_array_equal(dD, oracle.pack(dw, pr.T, N)[2])
 
 
+def _one_in(t):
+    """t as a contiguous view that starts one element into a larger buffer."""
+    v = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape)
+    return v.copy_(t)
+
+
+@pytest.mark.parametrize("n,m,k,s,B,H,W,N", [
+    (70, 130, 1, 1, 3, 8, 6, 32),        # (quads that the N = 32 kernels do not take at this alignment)
+    (70, 130, 1, 1, 3, 8, 6, 16),
+    (40, 130, 1, 1, 2, 9, 7, 32),
+    (64, 45, 3, 1, 2, 14, 15, 32),
+    (48, 24, 3, 2, 2, 11, 13, 16),
+])
+def test_bf16_misaligned_operands(n, m, k, s, B, H, W, N, tune):
+    """The 8- and 16-byte loads of x and dY at addresses of two bytes' alignment."""
+    tune("bwd_kernel", 4)
+    w, x = workloads.gen_integer_layer(n + m, n, m, k, B, H, W)
+    Ho, Wo = onexn.out_hw(H, W, k, k, (s, s), (k // 2, k // 2))
+    dy = torch.randint(-3, 4, (B, n, Ho, Wo), generator=torch.Generator().manual_seed(W)).float()
+    L = onexn.prepare_layer(w.bfloat16(), N, 0.5, True)
+    pr = oracle.prune(w.double().numpy(), N, 0.5, True)
+    xd, dyd = _one_in(x.bfloat16()), _one_in(dy.bfloat16())
+    at = ((s, s), (k // 2, k // 2))
+    y = L.forward(xd, s, k // 2, out_dtype=torch.float32)
+    np.testing.assert_array_equal(y.double().cpu().numpy(), oracle.conv2d(x.double().numpy(), pr.wbar, *at))
+    dx = onexn.conv2d_bwd_data(L.P, L.I, L.D, n, m, dyd, (H, W), s, k // 2, torch.float32)
+    np.testing.assert_array_equal(dx.double().cpu().numpy(),
+                                  oracle.conv2d_bwd_data(dy.double().numpy(), pr.wbar, (H, W), *at))
+    dD = onexn.conv2d_bwd_weight(L.P, L.I, n, N, (k, k), xd, dyd, s, k // 2)
+    dw = oracle.conv2d_bwd_weight(x.double().numpy(), dy.double().numpy(), pr.T, N, (k, k), *at)
+    np.testing.assert_array_equal(dD.double().cpu().numpy(), oracle.pack(dw, pr.T, N)[2])
+
+
 def test_bf16_weight_gradient_does_not_vary():
     w, x = workloads.gen_integer_layer(3, 64, 48, 3, 4, 20)
     x, dy = torch.randn(4, 48, 20, 20).bfloat16(), torch.randn(4, 64, 20, 20).bfloat16()
