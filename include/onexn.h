@@ -167,7 +167,9 @@ onexn_status onexn_pack(const void* w, onexn_dtype wdt, int32_t n, int32_t m, in
  * y_dev:  device output [batch][n][Ho][Wo] or [batch][Ho][Wo][n] (same layout
  *         as x), Ho = (H + 2*pad_h - kh)/stride_h + 1, likewise Wo.  Every
  *         element is written.  y must not overlap x, P, I or D.
- * dtypes: wdt == xdt (F32 or BF16); ydt == xdt or F32.
+ * dtypes: wdt == xdt (F32 or BF16); ydt == xdt or F32.  3x3 stride-1 F32
+ *         layers may run on three bf16 parts of each value, which hold it
+ *         exactly from 2^-110 on (below, to within 2^-134).
  * stream: hipStream_t to enqueue on (NULL = the null stream).  The call
  *         validates its arguments, launches, and returns without waiting.
  * Supported: N in {1, 2, 4, 8, 16, 32}; 1 <= kh, kw <= 16; stride 1..8;

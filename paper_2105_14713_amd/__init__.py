@@ -124,8 +124,9 @@ def _dtype_code(dt: torch.dtype) -> int:
 
 
 def _current_stream(t: torch.Tensor) -> int:
-    """torch's current stream on t's device.  The raw lookup costs 0.1 us, the
-    one through a Stream object 1.8, of a call's @T@."""
+    """torch's current stream on t's device.  The raw lookup, which torch has no
+    public name for, costs 0.1 us, the one through a Stream object 1.9, of the 7
+    that a call takes on the host."""
     return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 

@@ -404,8 +404,13 @@ extern "C" onexn_status onexn_conv2d_bwd_data(const int32_t* P_dev, const int32_
     // and all its channels.  bf16 1x1 layers at N >= 8: a kernel of their own.
     // 3x3 layers (fp32: stride 1) at N >= 8: the bf16-plane kernel (fp32 1x1
     // layers multiply too little per staged value for it: 64 -> 256 at 56x56,
-    // batch 64, 167 us against 96).  Other fp32 1x1 and 3x3 layers: the fp32
-    // matrix-core kernels.
+    // batch 64, 167 us against 96).  In fp32 it is the faster one also where its
+    // tiles are few: of 324 layers of 64 to 1024 channels at 7x7 to 56x56, batch
+    // 1 to 64, N = 8 to 32, p = 0.5, it took 0.47 to 0.88 of the fp32
+    // instruction's time (64 -> 64 at 7x7, batch 1, N = 32: 29.9 and 18.4 us; 256
+    // -> 64 at 56x56, batch 2: 31.4 and 27.6); its time does not depend on p, and
+    // at p = 0.97 three of 108 layers are 14 to 19 % slower.  Other fp32 1x1 and 3x3 layers: the
+    // fp32 matrix-core kernels.
     if (tuning(kTuneBwdKernel) != 1) {
         if (bwd_data_fewc_applies(a, wdt, dxdt, batch)) return launch_bwd_data_fewc(a, batch, dy_dev, dx_dev, s);
         if (bwd_data_pw_bf16_applies(a, wdt, batch))

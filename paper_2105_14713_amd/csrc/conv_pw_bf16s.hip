@@ -387,7 +387,7 @@ bool pw_bf16s_applies(const ConvArgs& a, onexn_dtype xdt, onexn_dtype ydt, onexn
 // 13.7 and 15.0, 512 -> 512 20.6 and 22.4; 1024 -> 4096 (83 % of four rounds)
 // 148 and 127; 1024 -> 1024 (42 % of two) 37.4 and 59.8; batch 160 (69 % of
 // three) 512 -> 1024 56.9 and 52.6, 1024 -> 1024 80.9 and 88.7, 2048 -> 1024
-// 153 and 136.
+// 153 and 136 (all three staged by the rule, the second at a loss).
 bool pw_bf16s_preferred(const ConvArgs& a) {
     if (a.m < 512) return false;
     const int64_t tiles = (int64_t(a.npix / a.HWo) * ((a.HWo + 7) / 8) + kSGran - 1) / kSGran;

@@ -34,10 +34,16 @@
 //                      counts the top 10 or 11 key bits, mask_hist the next 11 of
 //                      the keys under the pivot's top bits, mask_collect
 //                      lists the few keys left, mask_pivot ranks those (or,
-//                      with more than its list holds, as when very many scores
-//                      are equal, selects over all scores as mask_select
-//                      does).  The counts and the list live in the mask's own
-//                      bytes until mask_write overwrites them, and the pivot
+//                      with more than its list holds, selects over all scores
+//                      as mask_select does).  The list has 1024 entries (256
+//                      below 32768 blocks) however large the layer is; equal
+//                      scores outnumber it, and for normal weights those that
+//                      share the pivot's top 22 bits from some 1.1 million
+//                      blocks on at N = 32, 4.3 million at N = 1, and half a
+//                      million where a score is one bf16 weight (N = 1, 1x1:
+//                      1024 x 1024 4.6 ms; 5.9 before the selection was
+//                      spread).  The counts and the list live in the mask's
+//                      own bytes until mask_write overwrites them, and the pivot
 //                      in the workspace where the norms were, so the
 //                      workspace is no larger for it.  (A mask outside device
 //                      memory, which need not take atomics, is written once:
@@ -45,8 +51,8 @@
 //
 // 2048 -> 2048 at N = 32, fp32, rearranged (131072 blocks, 16.8 MB of
 // weights): 708 us with one wave per filter, a rank loop over eight
-// workgroups and one selecting workgroup (54 + 131 + 19 + 502); 64 us now (21 + 10 + 11, then
-// 5 + 6 + 9 + 4 for the selection).
+// workgroups and one selecting workgroup (54 + 131 + 19 + 502); 64 us now (21 +
+// 10 + 11, then 5 + 6 + 9 + 4 for the selection).
 // What bounds it now is the chain of dependent launches and, in the norms,
 // the sequential fp64 additions that bit-exactness asks for.
 //
