@@ -339,10 +339,15 @@ onexn_status launch_h(ConvArgs a, hipStream_t s) {
     // Column blocks per tile: two passes of kNBk blocks per wave, fewer where
     // the tile LDS or two workgroups per CU do not allow it.
     const int64_t fit = kNTileLds / nhwc_tile_bytes(kNCols, a.m);
-    // Layers with many tiles take four passes: 24 -> 144 at 56x56, batch 128
-    // (1568 tiles of 16 blocks, two sets of slices): 89 us against 115 with 8
-    // blocks; 32 -> 192 at 28x28 (392 tiles of 16): 31 against 27.
-    const int64_t passes = wpg == 1 && blocks * nsets >= 4 * kNBk * 8 * cus ? 4 : 2;
+    // Layers with many tiles take four passes where the LDS holds them whole and
+    // a block's row is long enough.  us with 8 and 16 blocks, N = 32: 24 -> 144 at
+    // 56x56, batch 128 85 and 68, with an epilogue 120 and 97; 16 -> 96 at
+    // 112x112, batch 64 79 and 92, with an epilogue 104 and 89; 96 -> 576 at
+    // 56x56, batch 64, of which 12 fit, 213 and 235 with these; 32 -> 192 at 28x28,
+    // batch 64 (392 tiles of 16) 27 and 31.
+    const bool four = wpg == 1 && blocks * nsets >= 4 * kNBk * 8 * cus && fit >= 4 * kNBk &&
+                      (a.m >= 24 || has_epilogue(a));
+    const int64_t passes = four ? 4 : 2;
     int64_t T = std::min<int64_t>({int64_t(kNMaxBlocks), fit, passes * kNBk * wpg});
     T = std::max<int64_t>(1, std::min<int64_t>(T, blocks * nsets / (2 * cus)));
     if (tuning(kTuneNhwcTile) >= 1)   // (at most what fits the CU's LDS)
