@@ -387,9 +387,12 @@ bool pw_bf16s_applies(const ConvArgs& a, onexn_dtype xdt, onexn_dtype ydt, onexn
 // 13.7 and 15.0, 512 -> 512 20.6 and 22.4; 1024 -> 4096 (83 % of four rounds)
 // 148 and 127; 1024 -> 1024 (42 % of two) 37.4 and 59.8; batch 160 (69 % of
 // three) 512 -> 1024 56.9 and 52.6, 1024 -> 1024 80.9 and 88.7, 2048 -> 1024
-// 153 and 136 (all three staged by the rule, the second at a loss).
+// 153 and 136 (all three staged by the rule, the second at a loss).  Images below
+// 64 pixels staged, with half a set: 4x4, batch 64: 512 -> 512 26.5 and 20.9, 600
+// -> 1000 31.2 and 23.9; 6x6: 21.1 and 20.7, 29.5 and 24.5.
 bool pw_bf16s_preferred(const ConvArgs& a) {
     if (a.m < 512) return false;
+    if (a.HWo < 64 && 2 * a.G >= kSCompute) return true;
     const int64_t tiles = (int64_t(a.npix / a.HWo) * ((a.HWo + 7) / 8) + kSGran - 1) / kSGran;
     const int64_t cus = device_cu_count(), items = tiles * ((a.G + kSCompute - 1) / kSCompute);
     const int64_t rounds = (items + cus - 1) / cus;
