@@ -354,23 +354,25 @@ bool dw_flat(const ConvArgs& a) { return a.KK == 1 && a.sh == 1 && a.sw == 1 && 
 
 // Whether a layer with strided columns, whose octets are loaded element by
 // element, is faster here than on the general kernel.  us fitted to both over
-// 690 layers: 0.07 per octet here, a fifth more of it per column that a short
-// row lacks; there 0.009 per pixel at N = 16 and 0.0175 at N = 32, and more
-// with the (block, tap) pairs, one workgroup each.  General and here, at stride
-// 2: 64 -> 64 1x1 at 7x7, batch 64: N = 16 12.0 and 33.2, N = 32 20.0 and 33.2;
-// at 28x28, batch 64: N = 16 158 and 133, N = 32 438 and 133; 256 -> 256 1x1 at
-// 7x7, batch 8, N = 16: 13.0 and 7.7; 64 -> 64 3x3 at 9x9, batch 64, N = 16:
-// 23.8 and 33.2.  The worst choice of the fit: 256 -> 64 3x3 at 7x7, batch 64, N
-// = 16, taken here at 54 against 42.
+// 1300 layers: 0.07 per octet here, less where a col-group's pairs do not fill a
+// tile, more by a sixth per column that a short row lacks; there, per pixel, by
+// the col-group's rows, and more with the (block, tap) pairs, one workgroup
+// each.  General and here, at stride 2: 64 -> 64 1x1 at 7x7, batch 64: N = 16
+// 12.0 and 33.2, N = 32 20.0 and 33.2; at 28x28, batch 64: N = 16 158 and 133, N
+// = 32 438 and 133; 256 -> 256 1x1 at 7x7, batch 8, N = 16: 13.0 and 7.7; 64 ->
+// 64 3x3 at 9x9, batch 64, N = 16: 23.8 and 33.2; 32 -> 8 3x3 at 28x28, batch 64,
+// N = 32: 78 and 130.  The worst choices of the fit, both taken here: 32 -> 8 1x1
+// at 56x56, batch 64, N = 16, 348 against 265; 256 -> 64 3x3 at 7x7, batch 64, N
+// = 16, 54 against 42.
 bool dw_strided_preferred(const ConvArgs& a, int32_t batch) {
     const double px = double(batch) * a.HWo, pairs = double(a.t) * a.KK, octs = double(batch) * a.Ho * ((a.Wo + 7) / 8);
-    const bool n16 = a.N == 16;
-    const double here = 2.8 + 0.0725 * octs * (1 + 0.15 * std::max(0, 8 - a.Wo));
-    const double per_px = std::max(n16 ? 0.009 : 0.0175, pairs * (n16 ? 0.8e-5 : 1.7e-5));
+    const double rows = std::min(a.N, a.n), fill = std::min(1.0, pairs / a.G / kDwPairs);
+    const double here = 2.8 + octs * (0.033 + 0.0395 * fill) * (1 + 0.15 * std::max(0, 8 - a.Wo));
+    const double per_px = rows * std::max(0.0005 * (1 + 2 / rows), pairs * 0.53e-6);
     // (It reads its operands once per pair: slower when an L2 does not hold them.)
     const double mb = 2e-6 * batch * (double(a.m) * a.H * a.W + double(a.n) * a.HWo);
     const double far = 1 + std::min(1.0, std::max(0.0, mb - 3) / 4);
-    const double general = 4.5 + pairs * (n16 ? 0.002 : 0.005) + px * far * (a.Wo < 5 ? 0.8 : 1.0) * per_px;
+    const double general = 4.5 + pairs * 0.00015 * rows + px * far * (a.Wo < 5 ? 0.8 : 1.0) * per_px;
     return here < general;
 }
 
