@@ -804,7 +804,10 @@ PlArgs pl_dx_args(const ConvArgs& a, int32_t batch, const void* dy, void* dx) {
 // batch 1 17.1 and 15.7, 32 20.0 and 16.4.
 bool pl_point_preferred(const ConvArgs& a, PlKind kind) {
     const double kept = double(a.t) / a.G, macs = double(a.npix) * a.t * a.N;
-    if (kind == kPlPointQuad) return a.HWo >= 16 || kept >= 56 || a.npix <= 32;
+    if (kind == kPlPointQuad) {
+        if (kept < 6 && a.npix <= 8192) return false;    // (3 -> 32 at 56x56, batch 1: 4.7 and 5.3)
+        return a.HWo >= 16 || kept >= 56 || a.npix <= 32;
+    }
     if (a.HWo < 16) return false;
     if (a.sh == 1) return (kept >= 56 && kept * a.npix >= 6000) || macs >= 5e7;
     return kept >= 112 || macs >= 2e8;
@@ -824,7 +827,16 @@ bool planes_fwd_applies(const ConvArgs& a, onexn_dtype xdt, onexn_dtype ydt, one
     const PlKind kind = pl_choose(p, a.kh, a.N);
     if (kind == kPlNone) return false;
     if (tuning(kTuneKernel) == 2) return true;
-    if (xdt == ONEXN_BF16) return a.kh != 1 || pl_point_preferred(a, kind);
+    if (xdt == ONEXN_BF16) {
+        if (a.kh == 1) return pl_point_preferred(a, kind);
+        // A chunk is 16 kept blocks, and a strided tile 128 pixels: image inputs of
+        // a few channels take less on the general kernel.  us there and here, 3x3
+        // stride 2 at 224x224, batch 8: 3 -> 32, N = 32 10.3 and 17.2, N = 16 22.5
+        // and 24.2; 6 -> 32, N = 32 12.2 and 17.3, N = 16 36.4 and 24.2; 3 -> 32 at
+        // 28x28, batch 64, N = 32: 7.5 and 6.9.
+        const bool few = a.m <= 3 || (a.N == 32 && 2 * int64_t(a.t) < 7 * a.G);
+        return a.sh == 1 || a.npix <= 2500 || !few;
+    }
     // fp32: against the fp32 instruction's kernel, which spreads a layer's
     // chunks over all compute units.  Times in us fitted to layers of 64 to
     // 512 channels at batch 1 to 256, at N = 32: a workgroup alone on its
@@ -863,6 +875,17 @@ bool planes_dx_applies(const ConvArgs& a, onexn_dtype wdt, int32_t batch) {
     if (a.N < 8 || a.kh != 3 || a.kw != 3 || a.sh != a.sw || (wdt == ONEXN_F32 && a.sh != 1)) return false;
     const int es = wdt == ONEXN_F32 ? 4 : 2;
     if (!pl_fits(a, batch, int64_t(a.n) * a.HWo, es, int64_t(batch) * a.H * (a.W + 8))) return false;
+    if (wdt == ONEXN_F32 && tuning(kTuneKernel) != 2) {
+        // Layers of few channels fill neither the 16-channel chunks nor the tile's
+        // 32 rows.  us, fp32 instruction and here, at 56x56, batch 16: 32 -> 8,
+        // N = 8 9.9 and 14.6, N = 16 13.5 and 14.9, N = 32 20.9 and 15.2; 144 -> 24,
+        // N = 8 45.4 and 51.3, N = 16 39.5 and 51.8, N = 32 64 and 51; 16 -> 16 at
+        // 28x28, batch 1, N = 8 11.8 and 10.1; 8 -> 64, N = 8 28.9 and 25.4, N = 16
+        // 23.5 and 25.0, N = 32 17.1 and 24.9 (28x28, batch 1: 16.7 and 17.5).
+        const bool few_px = int64_t(batch) * a.H * a.W <= (a.n <= 16 ? 20000 : 10000);
+        if (a.N < 32 && a.n <= 24 && !(few_px && (a.N == 16 || a.n > 8))) return false;
+        if (a.N == 32 && a.m <= 8) return false;
+    }
     PlArgs p = pl_dx_args(a, batch, nullptr, nullptr);
     return a.G <= kPlMaxRuns && pl_choose(p, 3, 32) != kPlNone;
 }

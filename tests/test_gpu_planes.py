@@ -88,6 +88,11 @@ BWD = [  # (n, m, k, stride, pad, B, H, W, N)
     (32, 5, 5, 1, 2, 1, 11, 23, 16),
     (32, 3, 7, 3, 3, 2, 25, 26, 32),
     (32, 600, 1, 1, 0, 40, 5, 5, 32),    # several chunks of 512 pixels
+    (8, 33, 3, 1, 1, 2, 11, 17, 8),      # few channels: kernels chosen by them
+    (24, 20, 3, 1, 1, 3, 61, 60, 16),
+    (64, 8, 3, 1, 1, 2, 9, 9, 32),
+    (8, 32, 1, 1, 0, 2, 9, 9, 8),
+    (8, 32, 3, 2, 1, 2, 15, 13, 32),
 ]
 
 
