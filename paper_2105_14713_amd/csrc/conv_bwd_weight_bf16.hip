@@ -8,9 +8,10 @@
 // one row of X per (kept block, tap) pair, pairs numbered tap-major.
 //
 // Work.  A workgroup computes the entries of 32 pairs and R rows of one
-// col-group (R = N, or half of N = 32 for layers of few tiles).  The contraction runs along the pixels, which are contiguous in both
-// operands, so a fragment entry is eight neighbouring pixels of a row: a lane
-// loads eight with one 16-byte load and stores them to LDS as they are;
+// col-group (R = N, or half of N = 32 for layers of few tiles).  The
+// contraction runs along the pixels, which are contiguous in both operands, so
+// a fragment entry is eight neighbouring pixels of a row: a lane loads eight
+// with one 16-byte load and stores them to LDS as they are;
 // nothing is transposed.  Octets are cut per output row (a 1x1 layer without
 // stride or padding is one row per image); the last one of a row is masked in
 // dY, and columns outside the image are masked in X.  Octets are stored
