@@ -290,7 +290,8 @@ bool bwd_data_pw_bf16_applies(const ConvArgs& a, onexn_dtype wdt, int32_t batch)
     // A chunk is 64 output channels: layers of few, over few pixels, take less on
     // the general kernel.  32 -> 8 at 7x7, batch 16, N = 8: 7.3 us there, 10.0
     // here; 28x28, batch 16: 10.9 and 8.2; 16 -> 16 at 7x7: 10.4 and 9.0.
-    if (a.n <= 8 && int64_t(batch) * a.H * a.W <= 8192) return false;
+    // (Its grid takes 65535 channels.)
+    if (a.n <= 8 && a.m <= 65535 && int64_t(batch) * a.H * a.W <= 8192) return false;
     return wdt == ONEXN_BF16 && a.KK == 1 && a.N >= 8 && a.sh == a.sw && a.G <= kBfMaxG &&
            reinterpret_cast<uintptr_t>(a.D) % 16 == 0 && int64_t(a.t) * a.N * 2 < (int64_t(1) << 31);
 }

@@ -789,10 +789,10 @@ PlArgs pl_dx_args(const ConvArgs& a, int32_t batch, const void* dy, void* dx) {
     return p;
 }
 
-// Whether a bf16 1x1 layer is faster here than on the general kernel (64-pixel
-// tiles).  A tile of 256 pixels has little to multiply in a layer of few pixels
-// or a short contraction, and one that spans images of a few pixels loads from
-// as many places as it has images.  us, general and here, p = 0.5, at stride 1:
+// Whether a bf16 1x1 layer is faster here than on the general kernel (tiles of
+// 128 pixels, 256 where they are many).  A chunk of 32 kept blocks has little to
+// multiply in a layer of few pixels or a short contraction, and a tile that spans
+// images of a few pixels loads from as many places as it has images.  us, general and here, p = 0.5, at stride 1:
 //   one-pixel images (samples of an FC layer), 2048 -> 1000, N = 32, batch 1:
 //     74 and 69, 128: 104 and 122, 512: 105 and 176; 256 -> 256, N = 16, 512:
 //     17.5 and 30.2; quads of 2x2 images, 64 -> 64, N = 16, batch 32: 6.6 and 7.1;
@@ -875,7 +875,7 @@ bool planes_dx_applies(const ConvArgs& a, onexn_dtype wdt, int32_t batch) {
     if (a.N < 8 || a.kh != 3 || a.kw != 3 || a.sh != a.sw || (wdt == ONEXN_F32 && a.sh != 1)) return false;
     const int es = wdt == ONEXN_F32 ? 4 : 2;
     if (!pl_fits(a, batch, int64_t(a.n) * a.HWo, es, int64_t(batch) * a.H * (a.W + 8))) return false;
-    if (wdt == ONEXN_F32 && tuning(kTuneKernel) != 2) {
+    if (wdt == ONEXN_F32 && tuning(kTuneKernel) != 2 && bwd_data_pw_applies(a, ONEXN_F32, ONEXN_F32, batch)) {
         // Layers of few channels fill neither the 16-channel chunks nor the tile's
         // 32 rows.  us, fp32 instruction and here, at 56x56, batch 16: 32 -> 8,
         // N = 8 9.9 and 14.6, N = 16 13.5 and 14.9, N = 32 20.9 and 15.2; 144 -> 24,

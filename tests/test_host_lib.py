@@ -316,5 +316,6 @@ def test_grid_limits_fall_back(lib):
     # 39.3 M output pixels x 32 col-groups: 128-pixel strided tiles are too many, 256-pixel ones are not.
     assert fwd(512, 8, 3, 16, 100, 600, 512, 512, 2) == ok
     assert dx(1, 1, 8, 1, 1, 32768, 36000) == ok                  # 1.2 G pixels of one channel
+    assert dx(8, 65536, 8, 1000, 1, 2, 2) == ok                   # (few output channels, more input ones than the general grid)
     assert dw(32 * 1100, 65536, 1, 32, 1000, 1, 2, 2) == ok       # 2048 tiles of 1100 col-groups
     assert dw(32 * 1000, 65536, 1, 32, 1000, 1, 2, 2) == ok       # (half the rows each would be too many)
